@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -19,7 +20,7 @@ ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}"]
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-SOURCES = ["kernels.hip", "host.cpp", "pcg.cpp"]
+SOURCES = ["kernels.hip", "wg.hip", "host.cpp", "pcg.cpp"]
 
 
 def _run(cmd, verbose):
@@ -36,8 +37,8 @@ def _run(cmd, verbose):
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
-    objs = []
-    for src in SOURCES:
+
+    def compile_one(src):
         obj = os.path.join(BUILD_DIR, src + ".o")
         path = os.path.join(CSRC, src)
         # host-only sources hold no device code: plain C++ (still through
@@ -48,7 +49,10 @@ def build(verbose: bool = False) -> str:
             rocm_inc = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(HIPCC))), "include")
             cmd = [HIPCC, *COMMON, "-x", "c++", "-D__HIP_PLATFORM_AMD__", f"-I{rocm_inc}", "-c", path, "-o", obj]
         _run(cmd, verbose)
-        objs.append(obj)
+        return obj
+
+    with ThreadPoolExecutor(max_workers=4) as pool:  # the sources are independent
+        objs = list(pool.map(compile_one, SOURCES))
     tmp = LIB + ".tmp"
     _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp, "-lpthread"], verbose)
     os.replace(tmp, LIB)
