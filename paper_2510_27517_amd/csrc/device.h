@@ -872,6 +872,31 @@ __device__ __forceinline__ void sum_partials(GLOBAL const double *__restrict__ p
   reduce_partials<NV>(acc, out, sh);
 }
 
+// The system a workgroup works for and its local index there. A launch over
+// one system (map = nullptr) takes the system's record as a kernel argument;
+// a launch over many looks its (system, local workgroup) up in the map and
+// the record in the directory. Both of those are dependent loads that miss
+// every cache after a kernel boundary (the first touch comes from memory), in
+// front of everything else a workgroup does: the argument takes two memory
+// round trips off each launch of a single solve.
+struct Work {
+  SysDev D;
+  int l;
+};
+__device__ __forceinline__ Work work_of(const SysDev *__restrict__ dir, const int2 *__restrict__ map,
+                                        const SysDev &one) {
+  Work w;
+  if (map) {
+    const int2 m = map[blockIdx.x];
+    w.D = dir[m.x];
+    w.l = m.y;
+  } else {
+    w.D = one;
+    w.l = (int)blockIdx.x;
+  }
+  return w;
+}
+
 // Rows [l n / G, (l+1) n / G) of a system: local workgroup l's share of
 // elementwise work over G workgroups.
 __device__ __forceinline__ void ew_rows(int n, int l, int G, int64_t &i0, int64_t &i1) {

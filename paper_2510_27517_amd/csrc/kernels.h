@@ -156,6 +156,9 @@ struct Types {
 // system helpers). All arrays are device-resident.
 struct LaunchSet {
   const SysDev *dir = nullptr;
+  // a launch over a single system: its record on the host, passed to the
+  // iteration and residual kernels as an argument (they then use no map)
+  const SysDev *one = nullptr;
   const int2 *mapA = nullptr, *mapGT = nullptr, *mapG = nullptr, *mapB = nullptr;
   const int32_t *set = nullptr;
   int32_t nA = 0, nGT = 0, nG = 0, nB = 0, nset = 0;  // workgroups of each kind, systems

@@ -55,11 +55,12 @@ namespace pcgk {
 // UW: loads in flight per lane in the one-row sliced walks (rows longer
 // than 4 entries), a tuning knob.
 template <typename TV, typename TA, int UW>
-__global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_iter_A(const SysDev *__restrict__ dir, const int2 *__restrict__ map) {
+__global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_iter_A(const SysDev *__restrict__ dir, const int2 *__restrict__ map, SysDev one) {
   __shared__ TV lds[kLdsBytes / sizeof(TV)];
   __shared__ Acc sh[4 * (kBlock / 64)];
-  const int2 m = map[blockIdx.x];
-  const SysDev &D = dir[m.x];
+  const Work wk = work_of(dir, map, one);
+  const SysDev &D = wk.D;
+  const int l = wk.l;
   GLOBAL const State &S = gl(D.st)[0];
   if (S.done) return;
   const Mat<TA> A = mat<TA>(D.A);
@@ -69,28 +70,29 @@ __global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_iter_A(const SysDev *_
   Acc part[1] = {{0.0, 0.0}};
   // pre's d_i[row] is the operand of A's diagonal
   for_rows<TV, UW, false, true>(
-      A, m.y, D.A.grid, lds, [&](int row) { return RowVals<TV>{dcur[row], (TV)0, (TV)0}; },
+      A, l, D.A.grid, lds, [&](int row) { return RowVals<TV>{dcur[row], (TV)0, (TV)0}; },
       [&](int j) -> TV { return dcur[j]; },
       [&](int row, TV sum, const RowVals<TV> &pv) {
         q[row] = sum;
         acc_prod(part[0], pv.a, sum);
       });
-  put_partials<1>(part, gl(D.pg), part_slot(m.y, D.A.grid), D.A.grid, sh);
+  put_partials<1>(part, gl(D.pg), part_slot(l, D.A.grid), D.A.grid, sh);
 }
 
 template <typename TV, typename TG>
-__global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_iter_GT(const SysDev *__restrict__ dir, const int2 *__restrict__ map,
+__global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_iter_GT(const SysDev *__restrict__ dir, const int2 *__restrict__ map, SysDev one,
                                                     int mode) {
   __shared__ TV lds[kLdsBytes / sizeof(TV)];
   __shared__ Acc sh[4 * (kBlock / 64)];
-  const int2 m = map[blockIdx.x];
-  const SysDev &D = dir[m.x];
+  const Work wk = work_of(dir, map, one);
+  const SysDev &D = wk.D;
+  const int l = wk.l;
   GLOBAL State *st = gl(D.st);
   GLOBAL const State &S = st[0];
   Acc g[1];
   load_partials<1>(gl(D.pg), D.A.grid, g);  // in flight while the state is read
   if (S.done) {  // stopped earlier: st[1] mirrors st[0], so the G-kernel need not read st[0]
-    if (m.y == 0 && threadIdx.x == 0) st_state(st + 1, ld_state(&S));
+    if (l == 0 && threadIdx.x == 0) st_state(st + 1, ld_state(&S));
     return;
   }
   const int it = S.iter;
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_iter_GT(const SysDe
     return !brk;
   };
   auto publish = [&]() {
-    if (m.y == 0 && threadIdx.x == 0) {
+    if (l == 0 && threadIdx.x == 0) {
       State o = ld_state(&S);
       o.gamma = gamma;
       o.alpha = alpha;
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_iter_GT(const SysDe
     };
     // pre2's pair equals gather_pair at offset 0 on every row that exists
     const bool go = for_rows2<TV, true, true>(
-        GT, m.y, D.GT.grid,
+        GT, l, D.GT.grid,
         [&](int r0, bool h0, bool h1) -> PV {
           PV o{{(TV)0, (TV)0}, {(TV)0, (TV)0}};
           if (h1) {
@@ -181,7 +183,7 @@ __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_iter_GT(const SysDe
   } else if (mode == 0) {
     publish();
     for_rows<TV, 4, true>(
-        GT, m.y, D.GT.grid, lds, [&](int row) { return RowVals<TV>{src[row], q[row], (TV)0}; },
+        GT, l, D.GT.grid, lds, [&](int row) { return RowVals<TV>{src[row], q[row], (TV)0}; },
         [&](int j) -> TV { return src[j] - al * q[j]; },
         [&](int row, TV sum, const RowVals<TV> &pv) {
           const TV rn = pv.a - al * pv.b;
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_iter_GT(const SysDe
   } else {
     publish();
     for_rows<TV, 4, true>(
-        GT, m.y, D.GT.grid, lds, [&](int row) { return RowVals<TV>{src[row], (TV)0, (TV)0}; },
+        GT, l, D.GT.grid, lds, [&](int row) { return RowVals<TV>{src[row], (TV)0, (TV)0}; },
         [&](int j) -> TV { return src[j]; },
         [&](int row, TV sum, const RowVals<TV> &pv) {
           t[row] = sum;
@@ -201,16 +203,17 @@ __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_iter_GT(const SysDe
           acc_prod(part[1], sum, sum);
         });
   }
-  put_partials<2>(part, gl(D.prt), part_slot(m.y, D.GT.grid), D.GT.grid, sh);
+  put_partials<2>(part, gl(D.prt), part_slot(l, D.GT.grid), D.GT.grid, sh);
 }
 
 template <typename TV, typename TG, bool HAS_EPS>
-__global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev *__restrict__ dir, const int2 *__restrict__ map,
+__global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev *__restrict__ dir, const int2 *__restrict__ map, SysDev one,
                                                    int mode) {
   __shared__ TV lds[kLdsBytes / sizeof(TV)];
   __shared__ Acc sh[4 * (kBlock / 64)];
-  const int2 m = map[blockIdx.x];
-  const SysDev &D = dir[m.x];
+  const Work wk = work_of(dir, map, one);
+  const SysDev &D = wk.D;
+  const int l = wk.l;
   GLOBAL State *st = gl(D.st);
   // st[1] is the G^T-kernel's publication for this iteration; st[0] is written
   // below by workgroup 0 and must not be read by the others
@@ -218,7 +221,7 @@ __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev 
   Acc va[2];
   load_partials<2>(gl(D.prt), D.GT.grid, va);  // in flight while the state is read
   if (S.done) {  // stopped earlier, or the G^T-kernel flagged a breakdown
-    if (m.y == 0 && threadIdx.x == 0) st_state(st, ld_state(&S));
+    if (l == 0 && threadIdx.x == 0) st_state(st, ld_state(&S));
     return;
   }
   const int it = S.iter;
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev 
       Pair<TV> r, d, x;
     };
     go = for_rows2<TV, false, false>(
-        G, m.y, D.G.grid,
+        G, l, D.G.grid,
         [&](int r0, bool h0, bool h1) -> PV {
           PV o{{(TV)0, (TV)0}, {(TV)0, (TV)0}, {(TV)0, (TV)0}};
           if (h1) {
@@ -299,7 +302,7 @@ __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev 
         step);
   } else if (upd)
     go = for_rows_h<TV>(
-        G, m.y, D.G.grid, lds,
+        G, l, D.G.grid, lds,
         [&](int row) { return RowVals<TV>{HAS_EPS ? rc[row] : (TV)0, dprev[row], x[row]}; },
         [&](int j) -> TV { return t[j]; },
         [&](int row, TV sum, const RowVals<TV> &pv) {
@@ -310,14 +313,14 @@ __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev 
         step);
   else
     go = for_rows_h<TV>(
-        G, m.y, D.G.grid, lds, [&](int row) { return RowVals<TV>{HAS_EPS ? rc[row] : (TV)0, dprev[row], (TV)0}; },
+        G, l, D.G.grid, lds, [&](int row) { return RowVals<TV>{HAS_EPS ? rc[row] : (TV)0, dprev[row], (TV)0}; },
         [&](int j) -> TV { return t[j]; },
         [&](int row, TV sum, const RowVals<TV> &pv) {
           const TV sv = HAS_EPS ? sum + eps * pv.a : sum;
           dnext[row] = sv + beta * pv.b;
         },
         step);
-  if (m.y == 0 && threadIdx.x == 0) {
+  if (l == 0 && threadIdx.x == 0) {
     State o = ld_state(&S);
     o.rr = rr;
     o.tt = tt;
@@ -335,18 +338,19 @@ __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev 
   }
   if (!go && upd) {  // stopped: x_{i+1} only
     int64_t i0, i1r;
-    ew_rows(D.n, m.y, D.G.grid, i0, i1r);
+    ew_rows(D.n, l, D.G.grid, i0, i1r);
     for (int64_t i = i0 + threadIdx.x; i < i1r; i += kBlock) x[i] = x[i] + ap * dprev[i];
   }
 }
 
 template <typename TV, typename TA>
-__global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_resid(const SysDev *__restrict__ dir, const int2 *__restrict__ map,
+__global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_resid(const SysDev *__restrict__ dir, const int2 *__restrict__ map, SysDev one,
                                                   int slot_sel, int with_d, int reduce, int respect_done) {
   __shared__ TV lds[kLdsBytes / sizeof(TV)];
   __shared__ Acc sh[4 * (kBlock / 64)];
-  const int2 m = map[blockIdx.x];
-  const SysDev &D = dir[m.x];
+  const Work wk = work_of(dir, map, one);
+  const SysDev &D = wk.D;
+  const int l = wk.l;
   GLOBAL const State &S = gl(D.st)[0];
   if (respect_done && S.done) return;
   const int it = S.iter;
@@ -374,10 +378,10 @@ __global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_resid(const SysDev *__
     acc_prod(part[0], rv, rv);
   };
   if (with_d)
-    for_rows<TV>(A, m.y, D.A.grid, lds, pre, [&](int j) -> TV { return x[j] + al * dc[j]; }, epi);
+    for_rows<TV>(A, l, D.A.grid, lds, pre, [&](int j) -> TV { return x[j] + al * dc[j]; }, epi);
   else
-    for_rows<TV>(A, m.y, D.A.grid, lds, pre, [&](int j) -> TV { return x[j]; }, epi);
-  if (reduce) put_partials<1>(part, gl(D.ptr), part_slot(m.y, D.A.grid), D.A.grid, sh);
+    for_rows<TV>(A, l, D.A.grid, lds, pre, [&](int j) -> TV { return x[j]; }, epi);
+  if (reduce) put_partials<1>(part, gl(D.ptr), part_slot(l, D.A.grid), D.A.grid, sh);
 }
 
 template <typename TV>
@@ -990,19 +994,25 @@ static inline int ew_grid(int64_t n) {
       hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, __VA_ARGS__);                   \
   } while (0)
 
+// A launch over one system passes its record (LaunchSet::one) instead of a map.
+#define PCG_ONE(lmap)                                  \
+  const SysDev one = L.one ? *L.one : SysDev{};        \
+  const int2 *map = L.one ? nullptr : (lmap)
+
 hipError_t launch_iter_A(const Types &ty, const LaunchSet &L, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (L.nA == 0) return hipSuccess;
   const bool u4 = L.uw_a == 4;
+  PCG_ONE(L.mapA);
   if (ty.vec == F64 && ty.a == F64) {
     if (u4)
-      PCG_LAUNCH((k_iter_A<double, double, 4>), L.nA, s, e0, e1, L.dir, L.mapA);
+      PCG_LAUNCH((k_iter_A<double, double, 4>), L.nA, s, e0, e1, L.dir, map, one);
     else
-      PCG_LAUNCH((k_iter_A<double, double, 8>), L.nA, s, e0, e1, L.dir, L.mapA);
+      PCG_LAUNCH((k_iter_A<double, double, 8>), L.nA, s, e0, e1, L.dir, map, one);
   } else if (ty.vec == F32 && ty.a == F32) {
     if (u4)
-      PCG_LAUNCH((k_iter_A<float, float, 4>), L.nA, s, e0, e1, L.dir, L.mapA);
+      PCG_LAUNCH((k_iter_A<float, float, 4>), L.nA, s, e0, e1, L.dir, map, one);
     else
-      PCG_LAUNCH((k_iter_A<float, float, 8>), L.nA, s, e0, e1, L.dir, L.mapA);
+      PCG_LAUNCH((k_iter_A<float, float, 8>), L.nA, s, e0, e1, L.dir, map, one);
   } else {
     return hipErrorInvalidValue;
   }
@@ -1012,8 +1022,9 @@ hipError_t launch_iter_A(const Types &ty, const LaunchSet &L, hipStream_t s, hip
 hipError_t launch_iter_GT(const Types &ty, const LaunchSet &L, int mode, hipStream_t s, hipEvent_t e0,
                           hipEvent_t e1) {
   if (L.nGT == 0) return hipSuccess;
+  PCG_ONE(L.mapGT);
   PCG_DISPATCH_V(ty.vec, TV, PCG_DISPATCH_G(ty.g, TG, {
-    PCG_LAUNCH((k_iter_GT<TV, TG>), L.nGT, s, e0, e1, L.dir, L.mapGT, mode);
+    PCG_LAUNCH((k_iter_GT<TV, TG>), L.nGT, s, e0, e1, L.dir, map, one, mode);
   }));
   return hipGetLastError();
 }
@@ -1021,11 +1032,12 @@ hipError_t launch_iter_GT(const Types &ty, const LaunchSet &L, int mode, hipStre
 hipError_t launch_iter_G(const Types &ty, const LaunchSet &L, bool has_eps, int mode, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1) {
   if (L.nG == 0) return hipSuccess;
+  PCG_ONE(L.mapG);
   PCG_DISPATCH_V(ty.vec, TV, PCG_DISPATCH_G(ty.g, TG, {
     if (has_eps)
-      PCG_LAUNCH((k_iter_G<TV, TG, true>), L.nG, s, e0, e1, L.dir, L.mapG, mode);
+      PCG_LAUNCH((k_iter_G<TV, TG, true>), L.nG, s, e0, e1, L.dir, map, one, mode);
     else
-      PCG_LAUNCH((k_iter_G<TV, TG, false>), L.nG, s, e0, e1, L.dir, L.mapG, mode);
+      PCG_LAUNCH((k_iter_G<TV, TG, false>), L.nG, s, e0, e1, L.dir, map, one, mode);
   }));
   return hipGetLastError();
 }
@@ -1033,11 +1045,12 @@ hipError_t launch_iter_G(const Types &ty, const LaunchSet &L, bool has_eps, int 
 hipError_t launch_resid(const Types &ty, const LaunchSet &L, int slot_sel, bool with_d, bool reduce,
                         bool respect_done, hipStream_t s) {
   if (L.nA == 0) return hipSuccess;
+  PCG_ONE(L.mapA);
   if (ty.vec == F64 && ty.a == F64) {
-    hipLaunchKernelGGL((k_resid<double, double>), dim3(L.nA), dim3(kBlock), 0, s, L.dir, L.mapA, slot_sel,
+    hipLaunchKernelGGL((k_resid<double, double>), dim3(L.nA), dim3(kBlock), 0, s, L.dir, map, one, slot_sel,
                        (int)with_d, (int)reduce, (int)respect_done);
   } else if (ty.vec == F32 && ty.a == F32) {
-    hipLaunchKernelGGL((k_resid<float, float>), dim3(L.nA), dim3(kBlock), 0, s, L.dir, L.mapA, slot_sel,
+    hipLaunchKernelGGL((k_resid<float, float>), dim3(L.nA), dim3(kBlock), 0, s, L.dir, map, one, slot_sel,
                        (int)with_d, (int)reduce, (int)respect_done);
   } else {
     return hipErrorInvalidValue;

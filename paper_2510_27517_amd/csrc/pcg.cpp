@@ -1060,8 +1060,10 @@ int single_sets(pcg_ctx *ctx) {
     ctx->dir[kSlot64] = ctx->single.dev64;
     if ((rc = upload_dir_entry(ctx, kSlot64))) return rc;
     if ((rc = build_set(ctx, ctx->set_64, {kSlot64}))) return rc;
+    ctx->set_64.L.one = &ctx->single.dev64;
   }
   if ((rc = build_set(ctx, ctx->set_main, {kSlotMain}))) return rc;
+  ctx->set_main.L.one = &ctx->single.dev;
   ctx->set_main.L.uw_a = ctx->tune.on ? ctx->tune.a_uw : cfg_loads_in_flight(ctx->cfg);
   return PCG_OK;
 }
@@ -1369,6 +1371,7 @@ int prepare_escalation(pcg_ctx *ctx) {
   ctx->dir[kSlotX] = D;
   int rc = upload_dir_entry(ctx, kSlotX);
   if (!rc) rc = build_set(ctx, ctx->set_x, {kSlotX});
+  if (!rc) ctx->set_x.L.one = &S.devx;
   return rc;
 }
 
