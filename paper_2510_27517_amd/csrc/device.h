@@ -746,45 +746,63 @@ __device__ __forceinline__ void acc_prod(Acc &x, float a, float b) {
   x.lo = x.lo + e;
 }
 
-// a + b, normalised (hi = fl(hi + lo))
+// a + b. The low words add plainly, without a renormalisation of the pair
+// (as each lane's own accumulation does: the bound above is Dot2's either
+// way): 8 FP64 operations, 6 of them dependent, instead of 14 and 12. The
+// reductions of one iteration are about a hundred of these one after the
+// other, two nanoseconds per operation.
 __device__ __forceinline__ Acc acc_add(Acc a, Acc b) {
-  double s, e;
-  two_sum(a.hi, b.hi, s, e);
-  const double t = (a.lo + b.lo) + e;
   Acc r;
-  two_sum(s, t, r.hi, r.lo);
+  double e;
+  two_sum(a.hi, b.hi, r.hi, e);
+  r.lo = (a.lo + b.lo) + e;
   return r;
 }
 
-// One DPP move of a double (two 32-bit moves); lanes of rows outside
-// ROW_MASK receive 0.
-template <int CTRL, int ROW_MASK>
+// One DPP move of a double (two 32-bit moves); lanes without a source
+// receive 0.
+template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
   const uint64_t b = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xF, false);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xF, false);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
-template <int CTRL, int ROW_MASK>
+template <int CTRL>
 __device__ __forceinline__ Acc acc_dpp(Acc a) {
-  return Acc{dpp_f64<CTRL, ROW_MASK>(a.hi), dpp_f64<CTRL, ROW_MASK>(a.lo)};
+  return Acc{dpp_f64<CTRL>(a.hi), dpp_f64<CTRL>(a.lo)};
 }
 
-// Wave total of a double-double by DPP row operations, with no LDS traffic.
-// The two quad exchanges, the half-row mirror and the row mirror leave each
-// 16-lane row's total in all of its lanes. Two row broadcasts then carry
-// rows 0 to 2 into row 3, so lanes 48-63 hold the total.
+// Wave total of a double-double by DPP row operations, with no LDS traffic,
+// in lane 63. The two quad exchanges, the half-row mirror and the row mirror
+// leave each 16-lane row's total in all of its lanes. Two row broadcasts then
+// carry rows 0 to 2 into row 3: lane 15 of each row into the next row (row 1
+// holds rows 0 + 1, row 3 rows 2 + 3), then lane 31 into rows 2 and 3. What
+// the other rows hold after that is not used.
 __device__ __forceinline__ Acc wave_total(Acc v) {
-  v = acc_add(v, acc_dpp<0xB1, 0xF>(v));   // quad_perm [1,0,3,2]
-  v = acc_add(v, acc_dpp<0x4E, 0xF>(v));   // quad_perm [2,3,0,1]
-  v = acc_add(v, acc_dpp<0x141, 0xF>(v));  // row_half_mirror
-  v = acc_add(v, acc_dpp<0x140, 0xF>(v));  // row_mirror
-  v = acc_add(v, acc_dpp<0x142, 0xA>(v));  // row_bcast:15 into rows 1 and 3
-  v = acc_add(v, acc_dpp<0x143, 0xC>(v));  // row_bcast:31 into rows 2 and 3
+  v = acc_add(v, acc_dpp<0xB1>(v));   // quad_perm [1,0,3,2]
+  v = acc_add(v, acc_dpp<0x4E>(v));   // quad_perm [2,3,0,1]
+  v = acc_add(v, acc_dpp<0x141>(v));  // row_half_mirror
+  v = acc_add(v, acc_dpp<0x140>(v));  // row_mirror
+  v = acc_add(v, acc_dpp<0x142>(v));  // row_bcast:15
+  v = acc_add(v, acc_dpp<0x143>(v));  // row_bcast:31
   return v;
 }
 
-// Workgroup total of each value, in thread 0 (normalised); sh[0, NV NW).
+// The wave totals in sh[0, NW) added pairwise.
+__device__ __forceinline__ Acc add_waves(const Acc *sh) {
+  constexpr int NW = kBlock / 64;
+  Acc a[NW];
+#pragma unroll
+  for (int q = 0; q < NW; ++q) a[q] = sh[q];
+#pragma unroll
+  for (int h = NW / 2; h >= 1; h /= 2)
+#pragma unroll
+    for (int q = 0; q < h; ++q) a[q] = acc_add(a[q], a[q + h]);
+  return a[0];
+}
+
+// Workgroup total of each value, in thread 0; sh[0, NV NW).
 template <int NV>
 __device__ __forceinline__ void block_sum(Acc (&v)[NV], Acc *sh) {
 #pragma unroll
@@ -797,11 +815,7 @@ __device__ __forceinline__ void block_sum(Acc (&v)[NV], Acc *sh) {
   __syncthreads();
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      Acc a = sh[j * NW];
-      for (int q = 1; q < NW; ++q) a = acc_add(a, sh[j * NW + q]);
-      v[j] = a;
-    }
+    for (int j = 0; j < NV; ++j) v[j] = add_waves(sh + j * NW);
   __syncthreads();
 }
 
@@ -858,8 +872,7 @@ __device__ __forceinline__ void reduce_partials(Acc (&acc)[NV], double (&out)[NV
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
-    Acc a = shr[j * NW];
-    for (int q = 1; q < NW; ++q) a = acc_add(a, shr[j * NW + q]);
+    const Acc a = add_waves(shr + j * NW);
     out[j] = uniform(a.hi + a.lo);
   }
 }
