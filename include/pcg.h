@@ -173,6 +173,10 @@ typedef struct {
  *        whose diagonal blocks are triangular, are stored as their 3x3-block
  *        cover (explicit zeros fill the missing entries) when the cover adds
  *        at most 1/8 of their nonzeros (at most 2x when BSR3 is forced).
+ *        A single solve whose A or G^T has at most 9 or 5 diagonals in all also
+ *        builds stencil storage for its iteration kernels from it (AUTO only;
+ *        device memory for one triangle of A and for G^T; without it the
+ *        sliced diagonals are used). Results are the same bit for bit.
  *  AUTO: BSR3 for such an A whose block padding stays within 1/8; otherwise
  *        SDIA when its stored values stay within 1/8 of the nonzeros, then
  *        SELL under the same rule, CSR otherwise. PCG_LAYOUT_SELL, _SDIA and
@@ -194,7 +198,11 @@ typedef struct {
   double bytes_per_iter; /* device bytes of one iteration in the layouts in use: A, G^T and G once
                             as stored (values with their padding; column information at its stored
                             width: 4 or 2 bytes per slot, one index per 3x3 block, one offset per
-                            sliced-diagonal entry; row or slice pointers), 11 vector streams */
+                            sliced-diagonal entry; row or slice pointers), 11 vector streams. A single
+                            system of few diagonals under the automatic layout is solved from one
+                            triangle of A (when A is symmetric bit for bit) and from G^T's values for
+                            both of the preconditioner's products (when G^T is lower triangular):
+                            then those are what is counted */
   double t_latency_ms; /* batched: submission to completion (host clock) */
   double t_queue_ms;   /* batched: submission to admission (host clock) */
   int escalated;       /* single solve under refinement: 1 when the inner solves switched to FP64 */

@@ -150,6 +150,33 @@ struct Types {
   int g;    // F64, F32, BF16 or F16
 };
 
+// ---- stencil storage of a single system (dia.hip)
+
+// A lower triangular matrix of nd diagonals: entry (r, r - dist[k]) at
+// val[k ld + r], 0 = dist[0] < dist[1] < ...; zero where the matrix has no
+// entry and in rows n <= r < ld, with ld at least n + dist[nd - 1] plus one
+// tile, so that entry (r + dist[k], r) can be read for every row r.
+constexpr int kDiaMax = 5;
+struct DiaOp {
+  void *val = nullptr;
+  int64_t ld = 0;
+  int32_t nd = 0;
+  int32_t dist[kDiaMax] = {0, 0, 0, 0, 0};
+  int32_t temporal = 0;  // 1: ordinary loads; 0: nontemporal
+};
+// Rows per lane with FP64 and FP32 vectors: 16-byte accesses either way
+// (against half as many, 128^3 FP64: A-kernel 16.4 us both, G^T 21.2 and 22.8,
+// G 22.4 and 22.7; 101^3 FP32 with a BF16 G: 5.5, 8.3 and 8.0 us against 6.3,
+// 8.5 and 10.0).
+constexpr int kDiaR64 = 2, kDiaR32 = 4;
+constexpr int kDiaTile = 64 * 4;  // rows of the largest tile
+struct DiaVecs {
+  void *x, *r0, *r1, *d0, *d1, *q, *t;
+  State *st;
+  double *pg, *prt;
+  int32_t n;
+};
+
 // One launch over a set of systems. Workgroup w of an A-kind launch (A, resid,
 // elementwise) works for system mapA[w].x as its local workgroup mapA[w].y;
 // likewise mapGT, mapG, mapB. `set` lists the systems (for one-thread-per-
@@ -162,6 +189,9 @@ struct LaunchSet {
   const int2 *mapA = nullptr, *mapGT = nullptr, *mapG = nullptr, *mapB = nullptr;
   const int32_t *set = nullptr;
   int32_t nA = 0, nGT = 0, nG = 0, nB = 0, nset = 0;  // workgroups of each kind, systems
+  // stencil storage of the single system's matrices, for the ordinary
+  // iterations (nd = 0: the general kernels)
+  DiaOp diaA, diaG;
   int32_t uw_a = 8;  // loads in flight per lane in the A-kernel's one-row sliced walks: 4 or 8
   // rows of the set's largest system whose seven iteration vectors fit in
   // the LDS cap with 8-byte and with 4-byte values (0: none): the
@@ -198,6 +228,22 @@ hipError_t launch_iter_GT(const Types &ty, const LaunchSet &L, int mode, hipStre
 // system stops at this iteration). Reads st[1] only.
 hipError_t launch_iter_G(const Types &ty, const LaunchSet &L, bool has_eps, int mode, hipStream_t s,
                          hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+
+// The three kernels of an ordinary iteration (mode 0) over stencil storage;
+// par: the parity of the iteration index i (it selects the r and d slots).
+// Grids and partial sums are those of the system's record (A.grid, GT.grid,
+// G.grid), so the general kernels can follow in the same solve.
+hipError_t launch_dia_A(const Types &ty, const DiaOp &A, const DiaVecs &v, int par, int grid, hipStream_t s,
+                        hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+hipError_t launch_dia_GT(const Types &ty, const DiaOp &B, const DiaVecs &v, int par, int gridA, int grid,
+                         hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+hipError_t launch_dia_G(const Types &ty, const DiaOp &B, const DiaVecs &v, bool has_eps, int par, int gridGT, int grid,
+                        hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+
+// Fills o (val allocated, ld, nd, dist set) from M, placed in sliced
+// diagonals. flag (device, cleared by the caller) set: flag[0] = 1 if M's
+// upper triangle differs from the transposed lower one in any bit.
+hipError_t launch_dia_build(const DevCSR &M, const DiaOp &o, int32_t *flag, hipStream_t s);
 
 // Whole PCG solves, one workgroup per system of the set (persistent: the
 // iteration loop, the residual replacement, the stopping test and, when

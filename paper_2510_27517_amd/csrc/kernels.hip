@@ -232,13 +232,13 @@ __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev 
   const bool upd = mode != 2;
   const TV ap = (TV)S.alpha;
   GLOBAL TV *__restrict__ x = gl((TV *)D.x);
-  GLOBAL const TV *__restrict__ dprev = gl((const TV *)((i1 & 1) ? D.d0 : D.d1));  // d_i
+  GLOBAL const TV *dprev = gl((const TV *)((i1 & 1) ? D.d0 : D.d1));  // d_i (may be d_{i+1}'s buffer)
   // s = G t + eps r, and the next direction d_{i+1} = s + beta d_i (at a
   // start or restart beta = 0, d = s)
   const Mat<TG> G = mat<TG>(D.G);
   GLOBAL const TV *__restrict__ t = gl((const TV *)D.t);
   GLOBAL const TV *__restrict__ rc = gl((const TV *)((i1 & 1) ? D.r1 : D.r0));
-  GLOBAL TV *__restrict__ dnext = gl((TV *)((i1 & 1) ? D.d1 : D.d0));
+  GLOBAL TV *dnext = gl((TV *)((i1 & 1) ? D.d1 : D.d0));
   const TV eps = (TV)eps_d;
   // delta_{i+1}, beta_i and the stopping tests, published in st[0]; false
   // once the solve stops (then only x is updated)

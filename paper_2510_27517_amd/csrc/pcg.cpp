@@ -306,6 +306,12 @@ struct Sys {
   SysDev dev64{};  // FP64 view for refinement (single path)
   SysDev devx{};   // FP64 inner solves after an escalation (single path; FP64 view of A, G as stored)
   void *blkA = nullptr, *blkG = nullptr, *blkX = nullptr;
+  // stencil storage for the single path's iteration kernels (dia.hip), and
+  // the column offsets of A and G^T it follows from (empty: too many)
+  void *blkD = nullptr;
+  void *d1 = nullptr;  // the second direction slot as placed
+  pcgk::DiaOp diaA, diaG;
+  std::vector<int32_t> offA, offGT;
   bool pooled = false;
   void *tmp_in = nullptr, *tmp_out = nullptr;
   double *stage64 = nullptr;
@@ -666,6 +672,7 @@ hipError_t place_a(const APart &P, void *block, Sys &S, const Copier &cp) {
   };
   void **vecs[] = {&S.dev.x, &S.dev.r0, &S.dev.r1, &S.dev.d0, &S.dev.d1, &S.dev.q, &S.dev.t, &S.dev.b};
   for (void **v : vecs) *v = c.take(vb);
+  S.d1 = S.dev.d1;
   S.dev.s = nullptr;  // s = G t + eps r is folded into d by the G-kernel
   S.dev.n = n;
   S.dev.gB = P.gB;
@@ -817,7 +824,7 @@ struct pcg_ctx {
   } tune;
   Sys single;
   HostSet set_main, set_64;
-  std::map<int, hipGraphExec_t> graphs;    // key: iters*2 + replace_first
+  std::map<int, hipGraphExec_t> graphs;    // key: iters*4 + parity of the first iteration*2 + replace_first
   std::map<int, hipGraphExec_t> graphs_x;  // the same for the escalated FP64 inner solves
   HostSet set_x;
   hipEvent_t ev[2] = {nullptr, nullptr}, t0 = nullptr, t1 = nullptr;
@@ -964,6 +971,7 @@ void free_sys(pcg_ctx *ctx, Sys &S) {
     ctx->da.put(S.blkA);
     ctx->da.put(S.blkG);
   }
+  ctx->da.put(S.blkD);
   ctx->da.put(S.blkX);
   S = Sys{};
 }
@@ -1036,6 +1044,101 @@ int residency_plan(const pcg_ctx *ctx) {
   return 0;
 }
 
+// The single system goes to the one-workgroup solver: small enough, and a
+// storage-type combination it is built for.
+bool use_solve_wg(const pcg_ctx *ctx, const Types &ty, int32_t n, bool batch = false) {
+  const int cf = batch ? ctx->cfg.wg_max_n_batch : ctx->cfg.wg_max_n;
+  const int lim = cf == 0 ? (batch ? kWgMaxNBatch : kWgMaxN) : cf;
+  return lim > 0 && n <= lim && pcgk::solve_wg_supported(ty);
+}
+
+// The distinct column offsets of a matrix laid out in sliced diagonals,
+// ascending; none when there are more than a stencil kernel takes.
+std::vector<int32_t> stencil_offsets(const HostMat &M) {
+  std::vector<int32_t> o;
+  if (M.fmt != pcgk::FMT_SDIA) return o;
+  for (int32_t d : M.ci) {
+    const auto it = std::lower_bound(o.begin(), o.end(), d);
+    if (it != o.end() && *it == d) continue;
+    if (o.size() >= 2 * pcgk::kDiaMax - 1) return {};
+    o.insert(it, d);
+  }
+  return o;
+}
+
+// Bytes of a matrix's stencil storage that one product reads.
+double stencil_bytes(const pcgk::DiaOp &o, const DevCSR &M) {
+  return (double)o.nd * M.n * (double)pcgk::dtype_size(M.dtype);
+}
+
+// Stencil storage of the single system (dia.hip), built on the device from
+// its sliced diagonals. A needs offsets in +- pairs and a diagonal, and must be
+// symmetric bit for bit (checked on the device); G^T must be lower triangular
+// with a diagonal (FSAI, Jacobi, the fixed and identity G). Each needs the
+// automatic layout and few enough diagonals, mostly full (within 1/8 of the
+// slots that the sliced diagonals store). Either may be used without the
+// other. Without the device memory for it the general kernels run.
+int build_stencil(pcg_ctx *ctx) {
+  Sys &S = ctx->single;
+  ctx->da.put(S.blkD);
+  S.blkD = nullptr;
+  S.diaA = S.diaG = pcgk::DiaOp{};
+  const int32_t n = S.n;
+  if (eff_cfg(ctx, false).layout != PCG_LAYOUT_AUTO || use_solve_wg(ctx, ctx->ty, n)) return PCG_OK;
+  auto shape = [&](const std::vector<int32_t> &off, const DevCSR &M, bool both, pcgk::DiaOp &o) {
+    const int nd = both ? ((int)off.size() + 1) / 2 : (int)off.size();
+    if (M.fmt != pcgk::FMT_SDIA || off.empty() || nd > pcgk::kDiaMax || (both && off.size() % 2 == 0)) return false;
+    for (int k = 0; k < nd; ++k) {
+      o.dist[k] = -off[nd - 1 - k];
+      if (both && off[nd - 1 + k] != o.dist[k]) return false;
+    }
+    if (o.dist[0] != 0) return false;
+    const int64_t slots = (int64_t)off.size() * n, sliced = M.nidx * pcgk::kSliceRows;
+    if (slots > sliced + sliced / 8) return false;
+    o.nd = nd;
+    // room for whole tiles and for the rows dist further on
+    o.ld = (((int64_t)n + pcgk::kDiaTile - 1) / pcgk::kDiaTile) * pcgk::kDiaTile + ((o.dist[nd - 1] + 63) / 64) * 64 + 64;
+    return true;
+  };
+  pcgk::DiaOp a, g;
+  const bool ha = shape(S.offA, S.dev.A, true, a);
+  const bool hg = eff_cfg(ctx, true).layout == PCG_LAYOUT_AUTO && S.dev.G.fmt == pcgk::FMT_SDIA &&
+                  shape(S.offGT, S.dev.GT, false, g);
+  if (!ha && !hg) return PCG_OK;
+  const size_t ba = ha ? align_up(pcgk::dtype_size(S.dev.A.dtype) * (size_t)(a.nd * a.ld)) : 0;
+  const size_t bg = hg ? align_up(pcgk::dtype_size(S.dev.GT.dtype) * (size_t)(g.nd * g.ld)) : 0;
+  void *blk = nullptr;
+  if (ctx->da.get(&blk, ba + bg + kAlign) != hipSuccess) {
+    (void)hipGetLastError();
+    return PCG_OK;
+  }
+  S.blkD = blk;
+  int32_t *flag = (int32_t *)((uint8_t *)blk + ba + bg), bad = 0;
+  a.val = blk;
+  g.val = (uint8_t *)blk + ba;
+  HIPCHK(pcgk::launch_fill(pcgk::F32, flag, 1, 0.0, ctx->stream));
+  if (ha) HIPCHK(pcgk::launch_dia_build(S.dev.A, a, flag, ctx->stream));
+  if (hg) HIPCHK(pcgk::launch_dia_build(S.dev.GT, g, nullptr, ctx->stream));
+  HIPCHK(hipMemcpyAsync(&bad, flag, sizeof bad, hipMemcpyDeviceToHost, ctx->stream));
+  HIPCHK(hipStreamSynchronize(ctx->stream));
+  if (ha && !bad) S.diaA = a;
+  if (hg) S.diaG = g;
+  // Load policy. Ordinary loads for both while one iteration's bytes (A's half,
+  // G once, and the vectors) fit in the memory-side cache: both matrices then
+  // stay there (128^3 FP64 65.4 us per iteration against 78.6 with nontemporal
+  // loads, 160^3 FP32 with a BF16 G 61.1 against 72.9). Above that A's
+  // alone (144^3 FP64 102.9 against 106.9 for both and 111.3 for none, 200^3
+  // 311.4, 312.6 and 315.7).
+  const double cap = (ctx->cfg.cache_mb > 0 ? ctx->cfg.cache_mb : 256) * 1048576.0;
+  const double bytes = stencil_bytes(S.diaA, S.dev.A) + stencil_bytes(S.diaG, S.dev.GT) +
+                       6.0 * n * (double)pcgk::dtype_size(ctx->ty.vec);
+  int keep = ctx->cfg.cache_mb < 0 ? 0 : bytes <= 0.95 * cap ? 3 : 1;
+  if (ctx->tune.on && ctx->tune.res >= 0) keep = (ctx->tune.res & 1) | ((ctx->tune.res & 6) ? 2 : 0);
+  S.diaA.temporal = keep & 1;
+  S.diaG.temporal = (keep >> 1) & 1;
+  return PCG_OK;
+}
+
 int single_sets(pcg_ctx *ctx) {
   drop_graphs(ctx);
   // the FP64 record of escalated inner solves refers to the placed G: rebuilt
@@ -1052,9 +1155,16 @@ int single_sets(pcg_ctx *ctx) {
     ctx->single.dev.G.rpl = ctx->single.dev.GT.rpl;
   }
   ctx->single.dev.st = ctx->d_states + 2 * kSlotMain;
+  ctx->single.dev.d1 = ctx->single.d1;
   ctx->dir[kSlotMain] = ctx->single.dev;
   int rc = upload_dir_entry(ctx, kSlotMain);
   if (rc) return rc;
+  if ((rc = build_stencil(ctx))) return rc;
+  if (ctx->single.diaG.nd) {  // its G-kernel reads and writes d row by row: one buffer will do
+    ctx->single.dev.d1 = ctx->single.dev.d0;
+    ctx->dir[kSlotMain] = ctx->single.dev;
+    if ((rc = upload_dir_entry(ctx, kSlotMain))) return rc;
+  }
   if (ctx->cfg.refine) {
     ctx->single.dev64.st = ctx->d_states + 2 * kSlot64;
     ctx->dir[kSlot64] = ctx->single.dev64;
@@ -1064,19 +1174,43 @@ int single_sets(pcg_ctx *ctx) {
   }
   if ((rc = build_set(ctx, ctx->set_main, {kSlotMain}))) return rc;
   ctx->set_main.L.one = &ctx->single.dev;
+  ctx->set_main.L.diaA = ctx->single.diaA;
+  ctx->set_main.L.diaG = ctx->single.diaG;
   ctx->set_main.L.uw_a = ctx->tune.on ? ctx->tune.a_uw : cfg_loads_in_flight(ctx->cfg);
   return PCG_OK;
 }
 
-void enqueue_iteration(pcg_ctx *ctx, const Types &ty, const LaunchSet &L, bool replace, double eps, hipError_t &e) {
+// Iteration `it` (its parity selects the r and d slots; the general kernels
+// read it from the state). ev: six events around the three kernels, or null.
+void enqueue_iteration(pcg_ctx *ctx, const Types &ty, const LaunchSet &L, int it, bool replace, double eps,
+                       hipError_t &e, const hipEvent_t *ev = nullptr) {
   auto chain = [&](hipError_t x) {
     if (e == hipSuccess) e = x;
   };
-  chain(pcgk::launch_iter_A(ty, L, ctx->stream));
-  if (replace) chain(pcgk::launch_resid(ty, L, 1, true, false, true, ctx->stream));
-  const int mode = replace ? 1 : 0;
-  chain(pcgk::launch_iter_GT(ty, L, mode, ctx->stream));
-  chain(pcgk::launch_iter_G(ty, L, eps != 0.0, mode, ctx->stream));
+  auto at = [&](int k) { return ev ? ev[k] : nullptr; };
+  hipStream_t s = ctx->stream;
+  const int par = it & 1;
+  pcgk::DiaVecs v{};
+  if (L.diaA.nd || L.diaG.nd) {
+    const SysDev &D = *L.one;
+    v = pcgk::DiaVecs{D.x, D.r0, D.r1, D.d0, D.d1, D.q, D.t, D.st, D.pg, D.prt, D.n};
+  }
+  if (L.diaA.nd)
+    chain(pcgk::launch_dia_A(ty, L.diaA, v, par, L.nA, s, at(0), at(1)));
+  else
+    chain(pcgk::launch_iter_A(ty, L, s, at(0), at(1)));
+  if (replace) {
+    chain(pcgk::launch_resid(ty, L, 1, true, false, true, s));
+    chain(pcgk::launch_iter_GT(ty, L, 1, s, at(2), at(3)));
+  } else if (L.diaG.nd) {
+    chain(pcgk::launch_dia_GT(ty, L.diaG, v, par, L.nA, L.nGT, s, at(2), at(3)));
+  } else {
+    chain(pcgk::launch_iter_GT(ty, L, 0, s, at(2), at(3)));
+  }
+  if (L.diaG.nd)
+    chain(pcgk::launch_dia_G(ty, L.diaG, v, eps != 0.0, par, L.nGT, L.nG, s, at(4), at(5)));
+  else
+    chain(pcgk::launch_iter_G(ty, L, eps != 0.0, replace ? 1 : 0, s, at(4), at(5)));
 }
 
 // What a single-system PCG runs on: the kernels' types, the launch set, the
@@ -1091,8 +1225,8 @@ struct Core {
 
 Core main_core(pcg_ctx *ctx) { return Core{ctx->ty, &ctx->set_main.L, &ctx->single.dev, kSlotMain, &ctx->graphs}; }
 
-int get_graph(pcg_ctx *ctx, const Core &c, int iters, bool replace_first, double eps, hipGraphExec_t *out) {
-  const int key = iters * 2 + (replace_first ? 1 : 0);
+int get_graph(pcg_ctx *ctx, const Core &c, int iters, int base, bool replace_first, double eps, hipGraphExec_t *out) {
+  const int par = base & 1, key = iters * 4 + par * 2 + (replace_first ? 1 : 0);
   auto it = c.graphs->find(key);
   if (it != c.graphs->end()) {
     *out = it->second;
@@ -1100,7 +1234,7 @@ int get_graph(pcg_ctx *ctx, const Core &c, int iters, bool replace_first, double
   }
   HIPCHK(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
-  for (int k = 0; k < iters; ++k) enqueue_iteration(ctx, c.ty, *c.L, replace_first && k == 0, eps, e);
+  for (int k = 0; k < iters; ++k) enqueue_iteration(ctx, c.ty, *c.L, par + k, replace_first && k == 0, eps, e);
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(ctx->stream, &g);
   HIPCHK(e);
@@ -1136,14 +1270,6 @@ int enqueue_start(pcg_ctx *ctx, const Types &ty, const LaunchSet &L, bool has_ep
 // residual meets tol, check b - A x and restart from it if that fails (the
 // inner solves of refinement skip this: the FP64 outer residual is the check,
 // and an FP32 iterate's true residual has a floor near u32 ||A|| ||x||).
-// The single system goes to the one-workgroup solver: small enough, and a
-// storage-type combination it is built for.
-bool use_solve_wg(const pcg_ctx *ctx, const Types &ty, int32_t n, bool batch = false) {
-  const int cf = batch ? ctx->cfg.wg_max_n_batch : ctx->cfg.wg_max_n;
-  const int lim = cf == 0 ? (batch ? kWgMaxNBatch : kWgMaxN) : cf;
-  return lim > 0 && n <= lim && pcgk::solve_wg_supported(ty);
-}
-
 int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out, bool confirm = true) {
   const Types &ty = c.ty;
   const LaunchSet &L = *c.L;
@@ -1200,13 +1326,13 @@ int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out,
         int len;
         if (K <= 0) {
           hipError_t e = hipSuccess;
-          enqueue_iteration(ctx, ty, L, rep, init.eps, e);
+          enqueue_iteration(ctx, ty, L, base, rep, init.eps, e);
           HIPCHK(e);
           len = 1;
         } else {
           len = (base % K == 0) ? K : 1;
           hipGraphExec_t g;
-          int rc = get_graph(ctx, c, len, rep, init.eps, &g);
+          int rc = get_graph(ctx, c, len, base, rep, init.eps, &g);
           if (rc) return rc;
           HIPCHK(hipGraphLaunch(g, s));
         }
@@ -1667,6 +1793,16 @@ double layout_bytes_per_iter(const SysDev &D, const pcg_config &cfg) {
                sv = (double)pcgk::dtype_size(cfg.vec_dtype);
   return stored_matrix_bytes(D.A, sa) + stored_matrix_bytes(D.G, sg) +
          stored_matrix_bytes(D.GT, sg) + 11.0 * D.n * sv;
+}
+
+// The same for the single system, whose iteration may read stencil storage:
+// half of A, and G^T's values for both of the preconditioner's products.
+double single_bytes_per_iter(const pcg_ctx *ctx) {
+  const Sys &S = ctx->single;
+  double b = layout_bytes_per_iter(S.dev, ctx->cfg);
+  if (S.diaA.nd) b += stencil_bytes(S.diaA, S.dev.A) - placed_bytes(S.dev.A);
+  if (S.diaG.nd) b += 2.0 * stencil_bytes(S.diaG, S.dev.GT) - placed_bytes(S.dev.G) - placed_bytes(S.dev.GT);
+  return b;
 }
 
 void finish_request(pcg_ctx *ctx, Req &R, int status, const State &f, int restarts) {
@@ -2535,6 +2671,7 @@ static int place_single_a(pcg_ctx *ctx) {
     return PCG_ENOMEM;
   }
   ctx->single.blkA = blk;
+  ctx->single.offA = stencil_offsets(P.A);
   HIPCHK(place_a(P, blk, ctx->single, Copier{Copier::Device, ctx->stream}));
   HIPCHK(hipStreamSynchronize(ctx->stream));
   ctx->have_a = true;
@@ -2618,6 +2755,7 @@ static int set_g_from_host(pcg_ctx *ctx, std::vector<int32_t> &grp, std::vector<
     return PCG_ENOMEM;
   }
   ctx->single.blkG = blk;
+  ctx->single.offGT = stencil_offsets(P.GT);
   HIPCHK(place_g(P, blk, ctx->single, Copier{Copier::Device, ctx->stream}));
   HIPCHK(hipStreamSynchronize(ctx->stream));
   int rc = single_sets(ctx);
@@ -2726,6 +2864,7 @@ static int build_fsai_device(pcg_ctx *ctx) {
     return PCG_ENOMEM;
   }
   S.blkG = blk;
+  S.offGT = stencil_offsets(P.GT);
   hipStream_t s = ctx->stream;
   Carver c{(uint8_t *)tmp};
   int32_t *d_rp = (int32_t *)c.take(4 * (size_t)(n + 1));
@@ -3112,7 +3251,7 @@ int pcg_solve(pcg_ctx *ctx, const double *b, double *x, double tol, int maxit, i
   HIPCHK(hipSetDevice(ctx->cfg.device));
   if (on_device) HIPCHK(hipDeviceSynchronize());
   HIPCHK(hipEventRecord(ctx->t0, ctx->stream));
-  const double bpi = layout_bytes_per_iter(S.dev, ctx->cfg);
+  const double bpi = single_bytes_per_iter(ctx);
   if (ctx->cfg.refine) {
     const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     HIPCHK(hipMemcpyAsync(S.dev64.b, b, sizeof(double) * n, kind, ctx->stream));
@@ -3350,10 +3489,7 @@ int pcg_time_kernels(pcg_ctx *ctx, int iters, double *ms, double *bytes) {
       if (e == hipSuccess) e = x;
     };
     for (int it = 0; it < iters; ++it) {
-      hipEvent_t *E = &ev[6 * (size_t)it];
-      chain(pcgk::launch_iter_A(ty, L, s, E[0], E[1]));
-      chain(pcgk::launch_iter_GT(ty, L, 0, s, E[2], E[3]));
-      chain(pcgk::launch_iter_G(ty, L, has_eps, 0, s, E[4], E[5]));
+      enqueue_iteration(ctx, ty, L, it, false, has_eps ? 1.0 : 0.0, e, &ev[6 * (size_t)it]);
     }
     chain(hipStreamSynchronize(s));
     for (int it = 0; it < iters && e == hipSuccess; ++it) {
@@ -3383,9 +3519,10 @@ int pcg_time_kernels(pcg_ctx *ctx, int iters, double *ms, double *bytes) {
   if (bytes) {
     const double sa = (double)pcgk::dtype_size(ctx->cfg.a_dtype), sg = (double)pcgk::dtype_size(ctx->cfg.g_dtype),
                  sv = (double)pcgk::dtype_size(ctx->cfg.vec_dtype);
-    bytes[0] = stored_matrix_bytes(S.dev.A, sa) + 2.0 * n * sv;
-    bytes[1] = stored_matrix_bytes(S.dev.GT, sg) + 4.0 * n * sv;
-    bytes[2] = stored_matrix_bytes(S.dev.G, sg) + (has_eps ? 6.0 : 5.0) * n * sv;
+    const double g = stencil_bytes(S.diaG, S.dev.GT);
+    bytes[0] = (S.diaA.nd ? stencil_bytes(S.diaA, S.dev.A) : stored_matrix_bytes(S.dev.A, sa)) + 2.0 * n * sv;
+    bytes[1] = (S.diaG.nd ? g : stored_matrix_bytes(S.dev.GT, sg)) + 4.0 * n * sv;
+    bytes[2] = (S.diaG.nd ? g : stored_matrix_bytes(S.dev.G, sg)) + (has_eps ? 6.0 : 5.0) * n * sv;
     bytes[3] = bytes[0] + bytes[1] + bytes[2];
   }
   return PCG_OK;
