@@ -132,7 +132,10 @@ typedef struct {
                         vectors stay in the workgroup's LDS when they fit (up to 2048 FP64 or 4096
                         FP32 rows here, 512 or 1024 in a batch, where the device allows it). One
                         workgroup has far less memory parallelism than a full launch, so this pays
-                        only for tiny systems. 0: the default (see pcg_config_default); -1: never */
+                        only for tiny systems. A system of few diagonals (at most 7 in A and 4 in
+                        G) keeps its matrices in registers as well; the default bound lets those
+                        run so up to 2048 rows (1024 in FP64 with more than 5 or 3 diagonals).
+                        0: the default (see pcg_config_default); -1: never */
   int wg_max_n_batch; /* the same for batched and served systems: those admitted in one scheduler
                         step run together, one workgroup each, in one launch on a second stream,
                         beside the iterations of the larger ones (many small systems keep the GPU

@@ -789,6 +789,50 @@ __device__ __forceinline__ Acc wave_total(Acc v) {
   return v;
 }
 
+// Wave totals of two double-doubles at once: a in lane 31, b in lane 63. One
+// exchange of wave halves leaves 32 partial sums of a in the lower half and 32
+// of b in the upper, so the remaining steps serve both (6 additions, not 12).
+__device__ __forceinline__ void swap_halves(double &a, double &b) {
+  const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  a = __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0]));
+  b = __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+__device__ __forceinline__ Acc wave_total2(Acc a, Acc b) {
+  swap_halves(a.hi, b.hi);
+  swap_halves(a.lo, b.lo);
+  Acc v = acc_add(a, b);
+  v = acc_add(v, acc_dpp<0xB1>(v));
+  v = acc_add(v, acc_dpp<0x4E>(v));
+  v = acc_add(v, acc_dpp<0x141>(v));
+  v = acc_add(v, acc_dpp<0x140>(v));
+  v = acc_add(v, acc_dpp<0x142>(v));
+  return v;
+}
+
+// A lane's double, in every lane.
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Each wave's totals of the NV values into sh[j NW + wave].
+template <int NV>
+__device__ __forceinline__ void put_wave_totals(const Acc (&v)[NV], Acc *sh) {
+  static_assert(NV == 1 || NV == 2, "values");
+  constexpr int NW = kBlock / 64;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if constexpr (NV == 1) {
+    const Acc t = wave_total(v[0]);
+    if (lane == 63) sh[w] = t;
+  } else {
+    const Acc t = wave_total2(v[0], v[1]);
+    if ((lane & 31) == 31) sh[(lane >> 5) * NW + w] = t;
+  }
+}
+
 // The wave totals in sh[0, NW) added pairwise.
 __device__ __forceinline__ Acc add_waves(const Acc *sh) {
   constexpr int NW = kBlock / 64;
@@ -805,13 +849,8 @@ __device__ __forceinline__ Acc add_waves(const Acc *sh) {
 // Workgroup total of each value, in thread 0; sh[0, NV NW).
 template <int NV>
 __device__ __forceinline__ void block_sum(Acc (&v)[NV], Acc *sh) {
-#pragma unroll
-  for (int j = 0; j < NV; ++j) v[j] = wave_total(v[j]);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   constexpr int NW = kBlock / 64;
-  if (lane == 63)
-#pragma unroll
-    for (int j = 0; j < NV; ++j) sh[j * NW + w] = v[j];
+  put_wave_totals<NV>(v, sh);
   __syncthreads();
   if (threadIdx.x == 0)
 #pragma unroll
@@ -863,12 +902,7 @@ __device__ __forceinline__ void reduce_partials(Acc (&acc)[NV], double (&out)[NV
   static_assert(NV <= 2, "reduction slots");
   constexpr int NW = kBlock / 64;
   Acc *shr = sh + 2 * NW;
-#pragma unroll
-  for (int j = 0; j < NV; ++j) acc[j] = wave_total(acc[j]);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 63)
-#pragma unroll
-    for (int j = 0; j < NV; ++j) shr[j * NW + w] = acc[j];
+  put_wave_totals<NV>(acc, shr);
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < NV; ++j) {

@@ -36,7 +36,7 @@ struct alignas(64) State {
   double true_rr;  // ||b - A x||^2 from the last true-residual kernel
   double bb;       // ||b||^2
   double tol;
-  double pad0;
+  double ticks;    // device time of a one-launch solve, in ticks of the constant-rate counter
   int32_t iter;       // completed iterations i
   int32_t maxit;
   int32_t status;     // Status below
@@ -259,6 +259,25 @@ hipError_t launch_dia_build(const DevCSR &M, const DiaOp &o, int32_t *flag, hipS
 // FP32, BF16 or FP16 G (others: hipErrorInvalidValue).
 bool solve_wg_supported(const Types &ty);
 hipError_t launch_solve_wg(const Types &ty, const LaunchSet &L, bool has_eps, hipStream_t s);
+
+// The same for one small stencil system with its matrices in registers
+// (wgs.hip): A, G^T and G placed in sliced diagonals with at most 7, 4 and 4
+// distinct column offsets in all, listed ascending; n <= wgs_max_n; pad at
+// least the largest |offset|; wgs_lds_bytes of dynamic LDS. b and x (x0 in,
+// solution out) are FP64 when io64, else of the vector type. The final
+// state goes to st[0] and to host (page-locked host memory).
+constexpr int kWgsMaxN = 2048, kWgsMaxA = 7, kWgsMaxG = 4;
+struct WgsArgs {
+  DevCSR A, GT, G;
+  const void *b = nullptr;
+  void *x = nullptr;
+  State *st = nullptr, *host = nullptr;
+  int32_t n = 0, pad = 0, io64 = 0, na = 0, nt = 0, ng = 0;
+  int32_t offA[kWgsMaxA] = {}, offT[kWgsMaxG] = {}, offG[kWgsMaxG] = {};
+};
+int32_t wgs_max_n(const Types &ty, int32_t na, int32_t ng);  // 0: not this kind of system
+size_t wgs_lds_bytes(int vec_dtype, int32_t n, int32_t pad);
+hipError_t launch_wgs(const Types &ty, const WgsArgs &P, const State &S0, hipStream_t s);
 
 // x += alpha d_{iter-1} if an update is still pending (alpha != 0), then
 // alpha = 0. The G-kernel applies every update itself and leaves alpha = 0, so

@@ -307,11 +307,11 @@ struct Sys {
   SysDev devx{};   // FP64 inner solves after an escalation (single path; FP64 view of A, G as stored)
   void *blkA = nullptr, *blkG = nullptr, *blkX = nullptr;
   // stencil storage for the single path's iteration kernels (dia.hip), and
-  // the column offsets of A and G^T it follows from (empty: too many)
+  // the column offsets of A, G^T and G it follows from (empty: too many)
   void *blkD = nullptr;
   void *d1 = nullptr;  // the second direction slot as placed
   pcgk::DiaOp diaA, diaG;
-  std::vector<int32_t> offA, offGT;
+  std::vector<int32_t> offA, offGT, offG;
   bool pooled = false;
   void *tmp_in = nullptr, *tmp_out = nullptr;
   double *stage64 = nullptr;
@@ -791,6 +791,7 @@ struct pcg_ctx {
   DevAlloc da;
   int cus = 256;
   int lds_per_block = 65536;  // the device's LDS bytes per workgroup
+  double ticks_per_ms = 1e5;  // the device's constant-rate counter
   std::string err;
   Types ty{};
 
@@ -1044,12 +1045,36 @@ int residency_plan(const pcg_ctx *ctx) {
   return 0;
 }
 
+// The largest distance from the diagonal in any of the system's matrices.
+int32_t wgs_pad(const Sys &S) {
+  int32_t p = 0;
+  for (const auto *o : {&S.offA, &S.offG, &S.offGT})
+    for (int32_t d : *o) p = std::max(p, std::abs(d));
+  return p;
+}
+
 // The single system goes to the one-workgroup solver: small enough, and a
 // storage-type combination it is built for.
 bool use_solve_wg(const pcg_ctx *ctx, const Types &ty, int32_t n, bool batch = false) {
   const int cf = batch ? ctx->cfg.wg_max_n_batch : ctx->cfg.wg_max_n;
   const int lim = cf == 0 ? (batch ? kWgMaxNBatch : kWgMaxN) : cf;
   return lim > 0 && n <= lim && pcgk::solve_wg_supported(ty);
+}
+
+// The single system goes to the one-workgroup solver with its matrices in
+// registers: stencils of few diagonals and at most 2048 rows, as far as they
+// fit in registers, unless pcg_config.wg_max_n sets another bound than its
+// default. Per iteration, the whole call, FP64: 8^2 rows 2.7 us against 10.9
+// with the matrices in memory and 19 for three launches; 45^2 3.3 against
+// 19 and 12.5; 10^3 4.0 against 19 and 17. It is ahead wherever it fits.
+bool use_wgs(const pcg_ctx *ctx, const Types &ty) {
+  const Sys &S = ctx->single;
+  const int cf = ctx->cfg.wg_max_n;
+  const int lim = cf == 0 || cf == kWgMaxN ? pcgk::kWgsMaxN : std::min(cf, pcgk::kWgsMaxN);
+  if (S.n > lim || S.offA.empty() || S.offG.empty() || S.offGT.empty()) return false;
+  if (S.dev.A.fmt != pcgk::FMT_SDIA || S.dev.G.fmt != pcgk::FMT_SDIA || S.dev.GT.fmt != pcgk::FMT_SDIA) return false;
+  if (S.n > pcgk::wgs_max_n(ty, (int32_t)S.offA.size(), (int32_t)std::max(S.offG.size(), S.offGT.size()))) return false;
+  return pcgk::wgs_lds_bytes(ty.vec, S.n, wgs_pad(S)) + 2048 <= (size_t)ctx->lds_per_block;
 }
 
 // The distinct column offsets of a matrix laid out in sliced diagonals,
@@ -1084,7 +1109,8 @@ int build_stencil(pcg_ctx *ctx) {
   S.blkD = nullptr;
   S.diaA = S.diaG = pcgk::DiaOp{};
   const int32_t n = S.n;
-  if (eff_cfg(ctx, false).layout != PCG_LAYOUT_AUTO || use_solve_wg(ctx, ctx->ty, n)) return PCG_OK;
+  if (eff_cfg(ctx, false).layout != PCG_LAYOUT_AUTO || use_wgs(ctx, ctx->ty) || use_solve_wg(ctx, ctx->ty, n))
+    return PCG_OK;
   auto shape = [&](const std::vector<int32_t> &off, const DevCSR &M, bool both, pcgk::DiaOp &o) {
     const int nd = both ? ((int)off.size() + 1) / 2 : (int)off.size();
     if (M.fmt != pcgk::FMT_SDIA || off.empty() || nd > pcgk::kDiaMax || (both && off.size() % 2 == 0)) return false;
@@ -1252,6 +1278,7 @@ struct CoreOut {
   int status = PCG_OK;
   int iters = 0, restarts = 0;
   double rr = 0, true_rr = 0, bb = 0;
+  double ms = 0;  // device time of a one-launch solve (use_wgs)
 };
 
 // Start sequence for the systems of L: ||b||, r = b - A x, t = G^T r,
@@ -1270,7 +1297,15 @@ int enqueue_start(pcg_ctx *ctx, const Types &ty, const LaunchSet &L, bool has_ep
 // residual meets tol, check b - A x and restart from it if that fails (the
 // inner solves of refinement skip this: the FP64 outer residual is the check,
 // and an FP32 iterate's true residual has a floor near u32 ||A|| ||x||).
-int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out, bool confirm = true) {
+// io: the caller's FP64 device vectors, for a solve that use_wgs takes (b and x
+// are then read and written there directly); else b and x are the system's.
+struct DirectIo {
+  const double *b;
+  double *x;
+};
+
+int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out, bool confirm = true,
+               const DirectIo *io = nullptr) {
   const Types &ty = c.ty;
   const LaunchSet &L = *c.L;
   SysDev &D = *c.dev;
@@ -1278,17 +1313,10 @@ int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out,
   State init = init_state(ctx, tol, maxit, ctx->single.g_scale, !confirm);
   const bool has_eps = init.eps != 0.0;
   init.confirm = confirm ? 1 : 0;
-  ctx->h_init[0] = init;
-  ctx->h_init[1] = init;
-  HIPCHK(hipMemcpyAsync(D.st, ctx->h_init, 2 * sizeof(State), hipMemcpyHostToDevice, s));
-  if (use_solve_wg(ctx, ty, D.n)) {  // the whole solve in one launch
-    HIPCHK(pcgk::launch_solve_wg(ty, L, has_eps, s));
-    State *hst = ctx->h_states + 2 * c.slot;
-    HIPCHK(hipMemcpyAsync(hst, D.st, sizeof(State), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    const State f = *hst;
+  auto one_launch = [&](const State &f) {
     out = CoreOut{};
-    if (f.status == pcgk::ST_ZERO_B) return PCG_OK;
+    out.ms = f.ticks / ctx->ticks_per_ms;
+    if (f.status == pcgk::ST_ZERO_B) return;
     out.iters = f.iter;
     out.rr = f.rr;
     out.true_rr = f.true_rr;
@@ -1297,6 +1325,40 @@ int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out,
     out.status = f.status == pcgk::ST_CONV_REC ? PCG_OK
                  : f.status == pcgk::ST_MAXIT  ? PCG_NOT_CONVERGED
                                                : PCG_EBREAKDOWN;
+  };
+  if (use_wgs(ctx, ty)) {
+    const Sys &S = ctx->single;
+    pcgk::WgsArgs P;
+    P.A = D.A;
+    P.GT = D.GT;
+    P.G = D.G;
+    P.b = io ? (const void *)io->b : D.b;
+    P.x = io ? (void *)io->x : D.x;
+    P.io64 = io != nullptr;
+    P.st = D.st;
+    P.host = ctx->h_states + 2 * c.slot;
+    P.n = D.n;
+    P.pad = wgs_pad(S);
+    P.na = (int32_t)S.offA.size();
+    P.nt = (int32_t)S.offGT.size();
+    P.ng = (int32_t)S.offG.size();
+    std::copy(S.offA.begin(), S.offA.end(), P.offA);
+    std::copy(S.offGT.begin(), S.offGT.end(), P.offT);
+    std::copy(S.offG.begin(), S.offG.end(), P.offG);
+    HIPCHK(pcgk::launch_wgs(ty, P, init, s));
+    HIPCHK(hipStreamSynchronize(s));
+    one_launch(*P.host);
+    return PCG_OK;
+  }
+  ctx->h_init[0] = init;
+  ctx->h_init[1] = init;
+  HIPCHK(hipMemcpyAsync(D.st, ctx->h_init, 2 * sizeof(State), hipMemcpyHostToDevice, s));
+  if (use_solve_wg(ctx, ty, D.n)) {  // the whole solve in one launch
+    HIPCHK(pcgk::launch_solve_wg(ty, L, has_eps, s));
+    State *hst = ctx->h_states + 2 * c.slot;
+    HIPCHK(hipMemcpyAsync(hst, D.st, sizeof(State), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    one_launch(*hst);
     return PCG_OK;
   }
   {
@@ -2583,6 +2645,9 @@ int pcg_create(const pcg_config *cfg, pcg_ctx **out) {
   if (hipGetDeviceProperties(&prop, cfg->device) == hipSuccess && prop.multiProcessorCount > 0) {
     ctx->cus = prop.multiProcessorCount;
     ctx->lds_per_block = (int)prop.sharedMemPerBlock;
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, cfg->device) == hipSuccess && khz > 0)
+      ctx->ticks_per_ms = khz;
   }
   if (cfg->stream) {
     ctx->stream = (hipStream_t)cfg->stream;
@@ -2756,6 +2821,7 @@ static int set_g_from_host(pcg_ctx *ctx, std::vector<int32_t> &grp, std::vector<
   }
   ctx->single.blkG = blk;
   ctx->single.offGT = stencil_offsets(P.GT);
+  ctx->single.offG = stencil_offsets(P.G);
   HIPCHK(place_g(P, blk, ctx->single, Copier{Copier::Device, ctx->stream}));
   HIPCHK(hipStreamSynchronize(ctx->stream));
   int rc = single_sets(ctx);
@@ -2865,6 +2931,7 @@ static int build_fsai_device(pcg_ctx *ctx) {
   }
   S.blkG = blk;
   S.offGT = stencil_offsets(P.GT);
+  S.offG = stencil_offsets(P.G);
   hipStream_t s = ctx->stream;
   Carver c{(uint8_t *)tmp};
   int32_t *d_rp = (int32_t *)c.take(4 * (size_t)(n + 1));
@@ -3250,8 +3317,30 @@ int pcg_solve(pcg_ctx *ctx, const double *b, double *x, double tol, int maxit, i
   int rc;
   HIPCHK(hipSetDevice(ctx->cfg.device));
   if (on_device) HIPCHK(hipDeviceSynchronize());
-  HIPCHK(hipEventRecord(ctx->t0, ctx->stream));
   const double bpi = single_bytes_per_iter(ctx);
+  auto finish = [&](const CoreOut &co, double ms) {
+    if (res) {
+      res->status = co.status;
+      res->iters = co.iters;
+      res->outer_iters = 0;
+      res->restarts = co.restarts;
+      res->relres_true = co.bb > 0 ? std::sqrt(co.true_rr / co.bb) : 0.0;
+      res->relres_rec = co.bb > 0 ? std::sqrt(co.rr / co.bb) : 0.0;
+      res->t_solve_ms = ms;
+      res->bytes_per_iter = bpi;
+    }
+    if (co.status == PCG_EBREAKDOWN) ctx->err = "breakdown: A or M not SPD, or non-finite values";
+    return co.status;
+  };
+  if (!ctx->cfg.refine && on_device && use_wgs(ctx, ctx->ty)) {
+    // one launch that reads b and x0 and writes x where the caller has them;
+    // its time comes from the device's counter, its state through host memory
+    const DirectIo io{b, x};
+    CoreOut co;
+    if ((rc = solve_core(ctx, main_core(ctx), tol, maxit, co, true, &io))) return rc;
+    return finish(co, co.ms);
+  }
+  HIPCHK(hipEventRecord(ctx->t0, ctx->stream));
   if (ctx->cfg.refine) {
     const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     HIPCHK(hipMemcpyAsync(S.dev64.b, b, sizeof(double) * n, kind, ctx->stream));
@@ -3279,18 +3368,7 @@ int pcg_solve(pcg_ctx *ctx, const double *b, double *x, double tol, int maxit, i
   if ((rc = store_vec(ctx, S.dev.x, ctx->ty.vec, x, on_device, n))) return rc;
   float ms = 0;
   HIPCHK(hipEventElapsedTime(&ms, ctx->t0, ctx->t1));
-  if (res) {
-    res->status = co.status;
-    res->iters = co.iters;
-    res->outer_iters = 0;
-    res->restarts = co.restarts;
-    res->relres_true = co.bb > 0 ? std::sqrt(co.true_rr / co.bb) : 0.0;
-    res->relres_rec = co.bb > 0 ? std::sqrt(co.rr / co.bb) : 0.0;
-    res->t_solve_ms = ms;
-    res->bytes_per_iter = bpi;
-  }
-  if (co.status == PCG_EBREAKDOWN) ctx->err = "breakdown: A or M not SPD, or non-finite values";
-  return co.status;
+  return finish(co, ms);
 }
 
 int pcg_matvec(pcg_ctx *ctx, int op, const double *x, double *y, int on_device) {

@@ -13,7 +13,7 @@ CSRC = os.path.join(ROOT, "paper_2510_27517_amd", "csrc")
 
 
 @pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="hipcc not installed")
-@pytest.mark.parametrize("source", ["wg.hip", "dia.hip"])
+@pytest.mark.parametrize("source", ["wg.hip", "dia.hip", "wgs.hip"])
 def test_no_spills(tmp_path, source):
     from paper_2510_27517_amd import build
 
