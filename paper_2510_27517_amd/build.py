@@ -20,7 +20,7 @@ ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}"]
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-SOURCES = ["kernels.hip", "wg.hip", "dia.hip", "wgs.hip", "host.cpp", "pcg.cpp"]
+SOURCES = ["kernels.hip", "wg.hip", "products.hip", "dia.hip", "wgs.hip", "host.cpp", "pcg.cpp"]
 
 
 def _run(cmd, verbose):

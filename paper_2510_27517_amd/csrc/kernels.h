@@ -297,11 +297,12 @@ hipError_t launch_outer(int vec_dtype, const LaunchSet &L64, int what, hipStream
 // done = 0, status = RUNNING, alpha = beta = 0 for every system of the set.
 hipError_t launch_state_restart(const LaunchSet &L, hipStream_t s);
 
-// y = M x for one stored matrix (plain product, vector type ty.vec).
-hipError_t launch_spmv(const Types &ty, const DevCSR &M, const void *x, void *y, hipStream_t s);
-
-// y = a*y + b*x (elementwise, vector type).
-hipError_t launch_axpby(int vec_dtype, int32_t n, double a, void *y, double b, const void *x, hipStream_t s);
+// y = M x for one stored matrix, rows summed in the vector type ty.vec; x and
+// y in FP64 or, for FP32 vectors, one of them in FP32 (converted at the gather
+// and at the store). z set (FP64): y = a (M x) + b z, in the vector type. y may
+// be z; it must not overlap x.
+hipError_t launch_spmv(const Types &ty, const DevCSR &M, int x_dtype, const void *x, int y_dtype, void *y,
+                       const double *z, double a, double b, hipStream_t s);
 
 // Conversions: dst[i] = (Tdst) (scale * src[i]).
 hipError_t launch_convert(int src_dtype, const void *src, int dst_dtype, void *dst, int64_t n, double scale,
@@ -339,18 +340,20 @@ hipError_t launch_fsai_place(const int32_t *rp, const int32_t *ci, const int32_t
 
 // ---- multi-probe products for the SAI loss (FP64 probes, n x k row-major)
 //
-// Y = c * (M X) + d * Z for a stored matrix M (either layout, any storage
-// type; Z may be null): one wave per row, lane p for probes p, p+64, ...;
-// each row summed left to right in CSR order.
-hipError_t launch_spmm(const DevCSR &M, int32_t k, const double *X, double c, const double *Z, double d, double *Y,
-                       hipStream_t s);
+// Y = c * (M X) + d * Z for a stored matrix M (any layout and storage type;
+// Z may be null), each row summed left to right in CSR order. k columns of
+// row-major vectors, ldx, ldz and ldy apart from row to row.
+constexpr int kSpmmGrid = 4096;
+hipError_t launch_spmm(const DevCSR &M, int32_t k, const double *X, int32_t ldx, double c, const double *Z,
+                       int32_t ldz, double d, double *Y, int32_t ldy, hipStream_t s);
 
-// Per-probe partial sums over rows for the losses: part[(b*5 + q)*k + p] for
+// Per-probe partial sums over rows for the losses, with Y = M X formed and
+// used at once (not stored; M in FP64 or FP32): part[(b*5 + q)*ldp + p] for
 // workgroup b < kLossGrid and q = 0..4: sum (y/na - w)^2, sum (y - w)^2,
 // sum w y, sum y^2, sum w^2 (probe p's columns of Y and W).
 constexpr int kLossGrid = 512;
-hipError_t launch_loss_partials(int32_t n, int32_t k, const double *W, const double *Y, double na, double *part,
-                                hipStream_t s);
+hipError_t launch_spmm_loss(const DevCSR &M, int32_t k, const double *X, int32_t ldx, const double *W, int32_t ldw,
+                            double na, double *part, int32_t ldp, hipStream_t s);
 
 // dst = src, `bytes` a multiple of 16 (nontemporal 16-byte accesses).
 hipError_t launch_copy(const void *src, void *dst, int64_t bytes, int grid, hipStream_t s);
@@ -368,9 +371,8 @@ hipError_t launch_read(const void *src, int64_t bytes, uint32_t *sink, int grid,
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
 hipError_t static_scratch(int device, void **ptr);
 
-// Final sums of the loss partials (kLossGrid x 5 x k, as launch_loss_partials
-// writes them): for each probe p, the five sums over the workgroups in
-// ascending order, then out[p] = sai, out[k + p] = l2 and
+// Final sums of the loss partials (kLossGrid x 5 x k, as launch_spmm_loss
+// writes them) in a fixed order, then for each probe p out[p] = sai, out[k + p] = l2 and
 // out[2k + p] = cs = (w^T y) / (sqrt(w^T w) sqrt(y^T y)).
 hipError_t launch_loss_final(int32_t k, const double *part, double *out, hipStream_t s);
 

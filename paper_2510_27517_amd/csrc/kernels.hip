@@ -495,21 +495,6 @@ __global__ __launch_bounds__(kBlock) void k_reduce_state(const SysDev *__restric
   }
 }
 
-template <typename TV, typename TM>
-__global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_spmv(DevCSR Md, const TV *__restrict__ x, TV *__restrict__ y) {
-  __shared__ TV lds[kLdsBytes / sizeof(TV)];
-  const Mat<TM> M = mat<TM>(Md);
-  for_rows<TV, 8>(
-      M, blockIdx.x, gridDim.x, lds, [&](int) { return RowVals<TV>{}; }, [&](int j) -> TV { return x[j]; },
-      [&](int row, TV sum, const RowVals<TV> &) { y[row] = sum; });
-}
-
-template <typename TV>
-__global__ void k_axpby(int32_t n, TV a, TV *__restrict__ y, TV b, const TV *__restrict__ x) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    y[i] = a * y[i] + b * x[i];
-}
-
 template <typename TS, typename TD>
 __global__ void k_convert(const TS *__restrict__ src, TD *__restrict__ dst, int64_t n, double scale) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -757,184 +742,6 @@ __global__ __launch_bounds__(kBlock) void k_fsai_place(const int32_t *__restrict
   }
 }
 
-// ------------------------------------------------ multi-probe products (SAI loss)
-
-template <typename TM>
-__device__ __forceinline__ double ld64(GLOBAL const TM *p, int64_t k) {
-  return (double)ldval(p, k);
-}
-__device__ __forceinline__ double ld64(GLOBAL const double *p, int64_t k) { return p[k]; }
-
-// LPR lanes per row (a power of two >= the probe count, up to 64): a wave
-// works on 64 / LPR rows at once, lane p of a group on probes p, p + LPR, ...
-// Each group loads four entries' columns and values ahead of their gathers;
-// the products are still added left to right.
-template <typename TM, int LPR, typename TI>
-__global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_spmm(DevCSR Md, int32_t k, const double *__restrict__ X_,
-                                                              double c, const double *__restrict__ Z_, double d,
-                                                              double *__restrict__ Y_) {
-  const Mat<TM> M = mat<TM>(Md);
-  GLOBAL const double *X = gl(X_);
-  GLOBAL const double *Z = Z_ ? gl(Z_) : nullptr;
-  GLOBAL double *Y = gl(Y_);
-  constexpr int RPW = 64 / LPR;  // rows per wave
-  constexpr int NW = kBlock / 64;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int grp = lane / LPR, pl = lane % LPR;
-  const int64_t rows_per_block = (int64_t)NW * RPW;
-  for (int64_t base = (int64_t)blockIdx.x * rows_per_block; base < M.n; base += (int64_t)gridDim.x * rows_per_block) {
-    const int64_t r = base + (int64_t)wv * RPW + grp;
-    const bool has = r < M.n;
-    const int32_t row = has ? (int32_t)r : 0;
-    int64_t e0 = 0, stride = 1;
-    int32_t len = 0;
-    if (has && M.fmt == FMT_SDIA) {  // one offset per slice entry; stored zeros add +0
-      const int32_t sl = row / kSliceRows, o0 = M.blk[sl], wd = M.blk[sl + 1] - o0;
-      GLOBAL const TM *vv = M.val + (int64_t)o0 * kSliceRows + row % kSliceRows;
-      for (int32_t p0 = 0; p0 < k; p0 += LPR) {
-        const int32_t p = p0 + pl;
-        double sum = 0.0;
-        for (int32_t e = 0; e < wd; ++e) {
-          const int32_t col = min(max(row + M.ci[o0 + e], 0), M.n - 1);
-          sum += ld64(vv, (int64_t)e * kSliceRows) * (p < k ? X[(int64_t)col * k + p] : 0.0);
-        }
-        if (p < k) {
-          double y = c * sum;
-          if (Z) y = y + d * Z[(int64_t)row * k + p];
-          Y[(int64_t)row * k + p] = y;
-        }
-      }
-      continue;
-    }
-    if (has && M.fmt == FMT_BSR3) {  // whole blocks: three entries of the row per block
-      const int32_t R = row / 3, sub = row % 3, sl = R / kBSliceRows, rr = R % kBSliceRows;
-      const int32_t o0 = M.blk[sl], wd = M.blk[sl + 1] - o0;
-      for (int32_t p0 = 0; p0 < k; p0 += LPR) {
-        const int32_t p = p0 + pl;
-        double sum = 0.0;
-        for (int32_t b = 0; b < wd; ++b) {
-          const int64_t blk = ((int64_t)o0 + b) * kBSliceRows + rr;
-          const int32_t c0 = 3 * M.ci[blk];
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            const int64_t vi = sizeof(TM) == 8 ? (((int64_t)o0 + b) * 3 + j) * (3 * kBSliceRows) + sub * kBSliceRows + rr
-                                               : (((int64_t)o0 + b) * kBSliceRows + rr) * 9 + 3 * sub + j;
-            const double a = ld64(M.val, vi);
-            sum += a * (p < k ? X[(int64_t)(c0 + j) * k + p] : 0.0);
-          }
-        }
-        if (p < k) {
-          double y = c * sum;
-          if (Z) y = y + d * Z[(int64_t)row * k + p];
-          Y[(int64_t)row * k + p] = y;
-        }
-      }
-      continue;
-    }
-    if (has) {
-      if (M.fmt == FMT_SELL) {  // padded entries add +0 (value 0, valid column)
-        const int32_t sl = row / kSliceRows;
-        e0 = (int64_t)M.blk[sl] * kSliceRows + row % kSliceRows;
-        stride = kSliceRows;
-        len = M.blk[sl + 1] - M.blk[sl];
-      } else {
-        e0 = M.rp[row];
-        len = M.rp[row + 1] - M.rp[row];
-      }
-    }
-    for (int32_t p0 = 0; p0 < k; p0 += LPR) {
-      const int32_t p = p0 + pl;
-      const bool act = has && p < k;
-      double sum = 0.0;
-      int32_t e = 0;
-      for (; e + 4 <= len; e += 4) {
-        int32_t col[4];
-        double a[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t q = e0 + (int64_t)(e + u) * stride;
-          col[u] = col_at<TI>(M.ci, q, row);
-          a[u] = ld64(M.val, q);
-        }
-        double x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = act ? X[(int64_t)col[u] * k + p] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) sum += a[u] * x[u];
-      }
-      for (; e < len; ++e) {
-        const int64_t q = e0 + (int64_t)e * stride;
-        const int32_t col = col_at<TI>(M.ci, q, row);
-        const double a = ld64(M.val, q);
-        sum += a * (act ? X[(int64_t)col * k + p] : 0.0);
-      }
-      if (act) {
-        double y = c * sum;
-        if (Z) y = y + d * Z[(int64_t)row * k + p];
-        Y[(int64_t)row * k + p] = y;
-      }
-    }
-  }
-}
-
-// Partial sums per workgroup (rows split in contiguous ranges), one lane per
-// probe, each sum in row order.
-__global__ __launch_bounds__(kBlock) void k_loss_partials(int32_t n, int32_t k, const double *__restrict__ W_,
-                                                          const double *__restrict__ Y_, double na,
-                                                          double *__restrict__ part_) {
-  __shared__ double sh[5 * kBlock];
-  GLOBAL const double *W = gl(W_), *Y = gl(Y_);
-  GLOBAL double *part = gl(part_);
-  const int64_t r0 = (int64_t)blockIdx.x * n / gridDim.x, r1 = (int64_t)(blockIdx.x + 1) * n / gridDim.x;
-  const int t = threadIdx.x;
-  const int lanes = kBlock;
-  for (int32_t p0 = 0; p0 < k; p0 += lanes) {
-    // thread t of group g = t / k2 handles probe p0 + t % k2 over rows r0 + g, r0 + g + ng, ...
-    const int32_t kk = min(lanes, k - p0);
-    const int ng = lanes / kk;
-    const int g = t / kk, p = p0 + t % kk;
-    double acc[5] = {0, 0, 0, 0, 0};
-    if (g < ng)
-      for (int64_t r = r0 + g; r < r1; r += ng) {
-        const double w = W[r * k + p], y = Y[r * k + p];
-        const double e = y / na - w, f = y - w;
-        acc[0] += e * e;
-        acc[1] += f * f;
-        acc[2] += w * y;
-        acc[3] += y * y;
-        acc[4] += w * w;
-      }
-#pragma unroll
-    for (int q = 0; q < 5; ++q) sh[q * kBlock + t] = (g < ng) ? acc[q] : 0.0;
-    __syncthreads();
-    if (t < kk) {  // fixed order over the groups
-      for (int q = 0; q < 5; ++q) {
-        double a = 0.0;
-        for (int gg = 0; gg < ng; ++gg) a += sh[q * kBlock + gg * kk + t];
-        part[((int64_t)blockIdx.x * 5 + q) * k + p0 + t] = a;
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// One thread per probe: the workgroups' partial sums added in ascending
-// workgroup order, then the three losses.
-__global__ __launch_bounds__(kBlock) void k_loss_final(int32_t k, const double *__restrict__ part_,
-                                                       double *__restrict__ out_) {
-  const int32_t p = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-  if (p >= k) return;
-  GLOBAL const double *part = gl(part_);
-  GLOBAL double *out = gl(out_);
-  double q[5] = {0, 0, 0, 0, 0};
-  for (int b = 0; b < kLossGrid; ++b)
-#pragma unroll
-    for (int j = 0; j < 5; ++j) q[j] += part[((int64_t)b * 5 + j) * k + p];
-  out[p] = q[0];
-  out[(int64_t)k + p] = q[1];
-  out[2 * (int64_t)k + p] = q[2] / (sqrt(q[4]) * sqrt(q[3]));
-}
-
 // The allocation-free entry point's scratch: one copy per device, allocated
 // by the runtime with the code object. Host code uses only the per-device
 // address that hipGetSymbolAddress returns for it.
@@ -1099,21 +906,6 @@ hipError_t launch_state_restart(const LaunchSet &L, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_spmv(const Types &ty, const DevCSR &M, const void *x, void *y, hipStream_t s) {
-  PCG_DISPATCH_V(ty.vec, TV, PCG_DISPATCH_G(M.dtype, TM, {
-    hipLaunchKernelGGL((k_spmv<TV, TM>), dim3(M.grid), dim3(kBlock), 0, s, M, (const TV *)x, (TV *)y);
-  }));
-  return hipGetLastError();
-}
-
-hipError_t launch_axpby(int vec_dtype, int32_t n, double a, void *y, double b, const void *x, hipStream_t s) {
-  PCG_DISPATCH_V(vec_dtype, TV, {
-    hipLaunchKernelGGL((k_axpby<TV>), dim3(ew_grid(n)), dim3(kBlock), 0, s, n, (TV)a, (TV *)y, (TV)b,
-                       (const TV *)x);
-  });
-  return hipGetLastError();
-}
-
 hipError_t launch_convert(int src_dtype, const void *src, int dst_dtype, void *dst, int64_t n, double scale,
                           hipStream_t s) {
   PCG_DISPATCH_V(src_dtype, TS, PCG_DISPATCH_V(dst_dtype, TD, {
@@ -1157,42 +949,6 @@ hipError_t launch_fsai_place(const int32_t *rp, const int32_t *ci, const int32_t
                              int32_t *err, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_fsai_place, dim3(ew_grid(n)), dim3(kBlock), 0, s, rp, ci, dpos, lrp, lv, n, scale, GT, G, err);
-  return hipGetLastError();
-}
-
-hipError_t launch_spmm(const DevCSR &M, int32_t k, const double *X, double c, const double *Z, double d, double *Y,
-                       hipStream_t s) {
-  if (M.n <= 0 || k <= 0) return hipSuccess;
-  const int lpr = k >= 64 ? 64 : k > 16 ? 32 : k > 8 ? 16 : 8;
-  const int64_t rows_per_block = (int64_t)(kBlock / 64) * (64 / lpr);
-  const int grid = (int)std::min<int64_t>(((int64_t)M.n + rows_per_block - 1) / rows_per_block, 65536);
-#define PCG_SPMM(L)                                                                                          \
-  PCG_DISPATCH_G(M.dtype, TM, {                                                                              \
-    if (M.idx16)                                                                                             \
-      hipLaunchKernelGGL((k_spmm<TM, L, int16_t>), dim3(grid), dim3(kBlock), 0, s, M, k, X, c, Z, d, Y);     \
-    else                                                                                                     \
-      hipLaunchKernelGGL((k_spmm<TM, L, int32_t>), dim3(grid), dim3(kBlock), 0, s, M, k, X, c, Z, d, Y);     \
-  })
-  switch (lpr) {
-    case 64: PCG_SPMM(64); break;
-    case 32: PCG_SPMM(32); break;
-    case 16: PCG_SPMM(16); break;
-    default: PCG_SPMM(8); break;
-  }
-#undef PCG_SPMM
-  return hipGetLastError();
-}
-
-hipError_t launch_loss_partials(int32_t n, int32_t k, const double *W, const double *Y, double na, double *part,
-                                hipStream_t s) {
-  if (n <= 0 || k <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_loss_partials, dim3(kLossGrid), dim3(kBlock), 0, s, n, k, W, Y, na, part);
-  return hipGetLastError();
-}
-
-hipError_t launch_loss_final(int32_t k, const double *part, double *out, hipStream_t s) {
-  if (k <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_loss_final, dim3((k + kBlock - 1) / kBlock), dim3(kBlock), 0, s, k, part, out);
   return hipGetLastError();
 }
 

@@ -313,8 +313,7 @@ struct Sys {
   pcgk::DiaOp diaA, diaG;
   std::vector<int32_t> offA, offGT, offG;
   bool pooled = false;
-  void *tmp_in = nullptr, *tmp_out = nullptr;
-  double *stage64 = nullptr;
+  double *stage64 = nullptr, *out64 = nullptr;  // FP64 staging of boundary vectors
 };
 
 int grid_for(int cus, int mult, int32_t units) {
@@ -561,7 +560,7 @@ void prep_a(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, const 
   const size_t vb = align_up(pcgk::dtype_size(P.vdt) * (size_t)n), db = align_up(8 * (size_t)n);
   size_t b = P.A.bytes() + 8 * vb;
   if (P.refine) b += b64 + 3 * db;
-  if (P.staging) b += 2 * vb + db;
+  if (P.staging) b += 2 * db;
   const int gtr = std::max(P.A.grid, P.refine ? P.grid64 : 0);
   constexpr size_t W = 8 * pcgk::kAccWords;  // bytes per partial sum
   b += align_up(W * (size_t)P.A.grid) + align_up(W * (size_t)gtr) + align_up(W * (size_t)P.gB);
@@ -711,9 +710,8 @@ hipError_t place_a(const APart &P, void *block, Sys &S, const Copier &cp) {
     D.gB = P.gB;
   }
   if (P.staging) {
-    S.tmp_in = c.take(vb);
-    S.tmp_out = c.take(vb);
     S.stage64 = (double *)c.take(8 * (size_t)n);
+    S.out64 = (double *)c.take(8 * (size_t)n);
   }
   return e;
 }
@@ -3381,29 +3379,69 @@ int pcg_matvec(pcg_ctx *ctx, int op, const double *x, double *y, int on_device) 
   Sys &S = ctx->single;
   const int32_t n = S.n;
   const int vdt = ctx->ty.vec;
-  int rc;
   HIPCHK(hipSetDevice(ctx->cfg.device));
   if (on_device) HIPCHK(hipDeviceSynchronize());
-  if ((rc = load_vec(ctx, x, on_device, S.tmp_in, vdt, n))) return rc;
   hipStream_t s = ctx->stream;
-  const double inv_scale2 = 1.0 / (S.g_scale * S.g_scale);
+  // Device vectors are read and written where they are; host vectors, and
+  // device vectors that overlap (a gathered entry must not have been
+  // overwritten), go through FP64 staging.
+  const size_t vb = sizeof(double) * (size_t)n;
+  const uintptr_t ux = (uintptr_t)x, uy = (uintptr_t)y;
+  const bool stage_x = !on_device || (ux < uy + vb && uy < ux + vb);
+  const double *xd = x;
+  double *yd = on_device ? y : S.out64;
+  if (stage_x) {
+    HIPCHK(hipMemcpyAsync(S.stage64, x, vb, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
+    xd = S.stage64;
+  }
+  const int F64 = pcgk::F64;
+  const double gs = S.g_scale;
   switch (op) {
-    case PCG_OP_A: HIPCHK(pcgk::launch_spmv(ctx->ty, S.dev.A, S.tmp_in, S.tmp_out, s)); break;
+    case PCG_OP_A: HIPCHK(pcgk::launch_spmv(ctx->ty, S.dev.A, F64, xd, F64, yd, nullptr, 0, 0, s)); break;
     case PCG_OP_GT:
-      HIPCHK(pcgk::launch_spmv(ctx->ty, S.dev.GT, S.tmp_in, S.tmp_out, s));
-      if (S.g_scale != 1.0) HIPCHK(pcgk::launch_axpby(vdt, n, 1.0 / S.g_scale, S.tmp_out, 0.0, S.tmp_in, s));
+    case PCG_OP_G: {
+      const DevCSR &M = op == PCG_OP_G ? S.dev.G : S.dev.GT;
+      HIPCHK(pcgk::launch_spmv(ctx->ty, M, F64, xd, F64, yd, gs != 1.0 ? xd : nullptr, 1.0 / gs, 0.0, s));
       break;
-    case PCG_OP_G:
-      HIPCHK(pcgk::launch_spmv(ctx->ty, S.dev.G, S.tmp_in, S.tmp_out, s));
-      if (S.g_scale != 1.0) HIPCHK(pcgk::launch_axpby(vdt, n, 1.0 / S.g_scale, S.tmp_out, 0.0, S.tmp_in, s));
-      break;
+    }
     default:
-      HIPCHK(pcgk::launch_spmv(ctx->ty, S.dev.GT, S.tmp_in, S.dev.t, s));
-      HIPCHK(pcgk::launch_spmv(ctx->ty, S.dev.G, S.dev.t, S.tmp_out, s));
-      HIPCHK(pcgk::launch_axpby(vdt, n, inv_scale2, S.tmp_out, ctx->cfg.eps, S.tmp_in, s));
+      HIPCHK(pcgk::launch_spmv(ctx->ty, S.dev.GT, F64, xd, vdt, S.dev.t, nullptr, 0, 0, s));
+      HIPCHK(pcgk::launch_spmv(ctx->ty, S.dev.G, vdt, S.dev.t, F64, yd, xd, 1.0 / (gs * gs), ctx->cfg.eps, s));
       break;
   }
-  return store_vec(ctx, S.tmp_out, vdt, y, on_device, n);
+  if (!on_device) HIPCHK(hipMemcpyAsync(y, yd, vb, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  return PCG_OK;
+}
+
+// The losses over k device probes W into out (3 k doubles): T = G^T W,
+// U = M^-1 W, and Y = A U used where it is formed. ||A|| = mean |A_ij| over the
+// nonzeros.
+static hipError_t enqueue_losses(pcg_ctx *ctx, int32_t k, const double *W, double *T, double *U, double *part,
+                                 double *out) {
+  const Sys &S = ctx->single;
+  hipStream_t s = ctx->stream;
+  const double eps = ctx->cfg.eps;
+  hipError_t e = hipSuccess;
+  auto chain = [&](hipError_t x) {
+    if (e == hipSuccess) e = x;
+  };
+  // Large blocks go in chunks of at most 32 columns, an odd last one of more
+  // than 15 without its last column, which follows alone: two columns per lane
+  // need an even count, and one per lane is slow (96^3, 33 probes: 555 us
+  // against 1302 in one piece, 31: 545 against 750; 7 in one piece: 168
+  // against 195). Small ones go whole: there each launch costs more than that.
+  const bool chunks = 8.0 * S.n * k > 32e6;
+  for (int32_t p = 0, m = 0; p < k; p += m) {
+    m = chunks ? std::min(32, k - p) : k;
+    if (chunks && m > 15 && m % 2) --m;
+    chain(pcgk::launch_spmm(S.dev.GT, m, W + p, k, 1.0, nullptr, 0, 0.0, T, m, s));
+    chain(pcgk::launch_spmm(S.dev.G, m, T, m, 1.0 / (S.g_scale * S.g_scale), eps != 0.0 ? W + p : nullptr, k, eps, U, m,
+                            s));
+    chain(pcgk::launch_spmm_loss(S.dev.A, m, U, m, W + p, k, ctx->a_mean_abs, part + p, k, s));
+  }
+  if (e == hipSuccess) e = pcgk::launch_loss_final(k, part, out, s);
+  return e;
 }
 
 int pcg_sai_loss(pcg_ctx *ctx, int32_t k, const double *W, int on_device, double *sai, double *l2, double *cs) {
@@ -3419,10 +3457,10 @@ int pcg_sai_loss(pcg_ctx *ctx, int32_t k, const double *W, int on_device, double
   HIPCHK(hipSetDevice(ctx->cfg.device));
   Sys &S = ctx->single;
   const int32_t n = S.n;
-  const double na = ctx->a_mean_abs;  // ||A|| = mean |A_ij| over the nonzeros
   const size_t nk = (size_t)n * (size_t)k;
   const size_t pb = sizeof(double) * (size_t)pcgk::kLossGrid * 5 * (size_t)k;
-  const size_t need = 3 * align_up(8 * nk) + align_up(pb);
+  // probes in device memory are read where they are
+  const size_t need = (on_device ? 2 : 3) * align_up(8 * nk) + align_up(pb) + align_up(8 * 3 * (size_t)k);
   if (need > ctx->loss_bytes) {
     ctx->da.put(ctx->loss_buf);
     ctx->loss_buf = nullptr;
@@ -3436,35 +3474,29 @@ int pcg_sai_loss(pcg_ctx *ctx, int32_t k, const double *W, int on_device, double
     ctx->loss_bytes = need;
   }
   Carver c{(uint8_t *)ctx->loss_buf};
-  double *Wd = (double *)c.take(8 * nk), *T = (double *)c.take(8 * nk), *U = (double *)c.take(8 * nk);
-  double *part = (double *)c.take(pb);
-  std::vector<double> hp((size_t)pcgk::kLossGrid * 5 * (size_t)k);
+  double *Wd = on_device ? nullptr : (double *)c.take(8 * nk);
+  double *T = (double *)c.take(8 * nk), *U = (double *)c.take(8 * nk);
+  double *part = (double *)c.take(pb), *out = (double *)c.take(8 * 3 * (size_t)k);
+  std::vector<double> h(3 * (size_t)k);
   hipStream_t s = ctx->stream;
   hipError_t e = hipSuccess;
   auto chain = [&](hipError_t x) {
     if (e == hipSuccess) e = x;
   };
-  if (on_device) chain(hipDeviceSynchronize());
-  chain(hipMemcpyAsync(Wd, W, 8 * nk, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
-  const double eps = ctx->cfg.eps;
-  chain(pcgk::launch_spmm(S.dev.GT, k, Wd, 1.0, nullptr, 0.0, T, s));  // T = G^T W
-  chain(pcgk::launch_spmm(S.dev.G, k, T, 1.0 / (S.g_scale * S.g_scale), eps != 0.0 ? Wd : nullptr, eps, U, s));
-  chain(pcgk::launch_spmm(S.dev.A, k, U, 1.0, nullptr, 0.0, T, s));  // Y = A M^-1 W
-  chain(pcgk::launch_loss_partials(n, k, Wd, T, na, part, s));
-  chain(hipMemcpyAsync(hp.data(), part, pb, hipMemcpyDeviceToHost, s));
+  if (on_device)
+    chain(hipDeviceSynchronize());
+  else
+    chain(hipMemcpyAsync(Wd, W, 8 * nk, hipMemcpyHostToDevice, s));
+  chain(enqueue_losses(ctx, k, on_device ? W : Wd, T, U, part, out));
+  chain(hipMemcpyAsync(h.data(), out, 8 * h.size(), hipMemcpyDeviceToHost, s));
   chain(hipStreamSynchronize(s));
   if (e != hipSuccess) {
     ctx->err = std::string("pcg_sai_loss: ") + hipGetErrorString(e);
     return PCG_EDEVICE;
   }
-  for (int32_t p = 0; p < k; ++p) {
-    double q[5] = {0, 0, 0, 0, 0};
-    for (int b = 0; b < pcgk::kLossGrid; ++b)
-      for (int j = 0; j < 5; ++j) q[j] += hp[((size_t)b * 5 + j) * k + p];
-    if (sai) sai[p] = q[0];
-    if (l2) l2[p] = q[1];
-    if (cs) cs[p] = q[2] / (std::sqrt(q[4]) * std::sqrt(q[3]));
-  }
+  if (sai) std::copy_n(h.data(), k, sai);
+  if (l2) std::copy_n(h.data() + k, k, l2);
+  if (cs) std::copy_n(h.data() + 2 * (size_t)k, k, cs);
   return PCG_OK;
 }
 
@@ -3506,12 +3538,7 @@ int pcg_sai_loss_noalloc(pcg_ctx *ctx, int32_t k, const double *W, double *sai, 
     if (e == hipSuccess) e = x;
   };
   chain(hipDeviceSynchronize());  // W may come from work queued on another stream
-  const double eps = ctx->cfg.eps;
-  chain(pcgk::launch_spmm(S.dev.GT, k, W, 1.0, nullptr, 0.0, T, s));  // T = G^T W
-  chain(pcgk::launch_spmm(S.dev.G, k, T, 1.0 / (S.g_scale * S.g_scale), eps != 0.0 ? W : nullptr, eps, U, s));
-  chain(pcgk::launch_spmm(S.dev.A, k, U, 1.0, nullptr, 0.0, T, s));  // Y = A M^-1 W
-  chain(pcgk::launch_loss_partials(n, k, W, T, ctx->a_mean_abs, part, s));
-  chain(pcgk::launch_loss_final(k, part, out, s));
+  chain(enqueue_losses(ctx, k, W, T, U, part, out));
   double *dst[3] = {sai, l2, cs};
   for (int j = 0; j < 3; ++j)
     if (dst[j]) chain(hipMemcpyAsync(dst[j], out + (size_t)j * k, 8 * (size_t)k, hipMemcpyDeviceToHost, s));
