@@ -322,6 +322,7 @@ hipError_t launch_refine_update(int32_t n, double *x64, const void *c, int c_dty
 // of the host builder in the same order. err[0] = 1 on a non-positive pivot.
 // mmax (the longest tril row) sizes the LDS: at most kFsaiMaxRow.
 constexpr int kFsaiMaxRow = 80;
+constexpr int kFsaiShortRow = 8;  // longest tril row that one thread factors (36 KiB of LDS per wave)
 hipError_t launch_fsai_rows(const int32_t *rp, const int32_t *ci, const double *v, const int32_t *dpos,
                             const int32_t *lrp, int32_t n, int32_t mmax, double *lv, int32_t *err, int grid,
                             hipStream_t s);
