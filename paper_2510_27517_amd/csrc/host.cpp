@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <atomic>
 #include <thread>
 
 #include <sched.h>
@@ -16,7 +17,12 @@ namespace pcgh {
 
 // ------------------------------------------------------------ host helpers
 
-int validate_csr(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *ci, int require_diag, std::string *why) {
+// Rows per thread below which another thread does not pay (about 20 us to
+// start one, a few ns per entry).
+constexpr int64_t kRowGrain = 16384;
+
+int validate_csr(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *ci, int require_diag, std::string *why,
+                 int threads) {
   auto fail = [&](const char *m, int64_t i) {
     if (why) {
       char buf[160];
@@ -29,6 +35,25 @@ int validate_csr(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *ci, i
   if (n > 0 && (!rp || (nnz > 0 && !ci))) return fail("null CSR array", 0);
   if (n == 0) return nnz == 0 ? PCG_OK : fail("nnz > 0 with n = 0", nnz);
   if (rp[0] != 0) return fail("rowptr[0] != 0", 0);
+  // large matrices on several threads first; whatever is wrong is then found
+  // and named by the ordinary pass
+  if (part_count(threads, n, kRowGrain) > 1) {
+    std::atomic<bool> bad{false};
+    parallel_parts(threads, n, kRowGrain, [&](int64_t lo, int64_t hi, int) {
+      bool ok = true;
+      for (int64_t i = lo; i < hi && ok; ++i) {
+        bool diag = false;
+        ok = rp[i] >= 0 && rp[i + 1] >= rp[i] && rp[i + 1] <= nnz;
+        for (int64_t k = rp[i]; ok && k < rp[i + 1]; ++k) {
+          ok = ci[k] >= 0 && ci[k] < n && (k == rp[i] || ci[k] > ci[k - 1]);
+          diag |= ci[k] == i;
+        }
+        ok = ok && (diag || !require_diag);
+      }
+      if (!ok) bad = true;
+    });
+    if (!bad && rp[n] == nnz) return PCG_OK;
+  }
   for (int32_t i = 0; i < n; ++i) {
     if (rp[i + 1] < rp[i]) return fail("rowptr decreases", i);
     bool diag = false;
@@ -425,9 +450,10 @@ void sell_columns(int32_t n, const int32_t *rp, const int32_t *ci, const std::ve
 }
 
 void sell_bytes(int32_t n, const int32_t *rp, const uint8_t *in, size_t esz, const std::vector<int32_t> &so,
-                std::vector<uint8_t> &out) {
+                Bytes &out) {
   const int32_t ns = (int32_t)so.size() - 1;
-  out.assign((size_t)so[ns] * kSlice * esz, 0);
+  out.resize((size_t)so[ns] * kSlice * esz);
+  std::fill(out.begin(), out.end(), uint8_t(0));
   for (int32_t r = 0; r < n; ++r) {
     const int32_t c = r / kSlice, l = r % kSlice;
     for (int32_t k = 0; k < rp[r + 1] - rp[r]; ++k)
@@ -437,11 +463,17 @@ void sell_bytes(int32_t n, const int32_t *rp, const uint8_t *in, size_t esz, con
 
 // The distinct offsets of slice c's entries, ascending.
 static void slice_offsets(int32_t n, const int32_t *rp, const int32_t *ci, int32_t c, std::vector<int32_t> &d) {
+  // rows and d are ascending: each row merges into d, which after a stencil's
+  // first row already holds (nearly) all of the slice's offsets
   d.clear();
-  for (int32_t r = c * kSlice; r < std::min(n, (c + 1) * kSlice); ++r)
-    for (int32_t k = rp[r]; k < rp[r + 1]; ++k) d.push_back(ci[k] - r);
-  std::sort(d.begin(), d.end());
-  d.erase(std::unique(d.begin(), d.end()), d.end());
+  for (int32_t r = c * kSlice; r < std::min(n, (c + 1) * kSlice); ++r) {
+    size_t k = 0;
+    for (int32_t q = rp[r]; q < rp[r + 1]; ++q, ++k) {
+      const int32_t o = ci[q] - r;
+      while (k < d.size() && d[k] < o) ++k;
+      if (k == d.size() || d[k] != o) d.insert(d.begin() + k, o);
+    }
+  }
 }
 
 int64_t sdia_entries(int32_t n, const int32_t *rp, const int32_t *ci, int64_t stop) {
@@ -455,31 +487,76 @@ int64_t sdia_entries(int32_t n, const int32_t *rp, const int32_t *ci, int64_t st
   return tot;
 }
 
-void sdia_pattern(int32_t n, const int32_t *rp, const int32_t *ci, std::vector<int32_t> &so,
-                  std::vector<int32_t> &offs) {
+bool sdia_pattern(int32_t n, const int32_t *rp, const int32_t *ci, int64_t cap, std::vector<int32_t> &so,
+                  std::vector<int32_t> &offs, int threads) {
   const int32_t ns = (n + kSlice - 1) / kSlice;
+  const int64_t grain = kRowGrain / kSlice;
   so.assign(ns + 1, 0);
+  std::vector<std::vector<int32_t>> part(part_count(threads, ns, grain));
+  std::atomic<int64_t> stored{0};
+  parallel_parts(threads, ns, grain, [&](int64_t lo, int64_t hi, int t) {
+    std::vector<int32_t> d;
+    std::vector<int32_t> &mine = part[t];
+    for (int64_t c = lo; c < hi; ++c) {
+      slice_offsets(n, rp, ci, (int32_t)c, d);
+      mine.insert(mine.end(), d.begin(), d.end());
+      so[c + 1] = (int32_t)d.size();
+      if ((stored += (int64_t)d.size() * kSlice) > cap) return;
+    }
+  });
+  if (stored > cap || stored / kSlice > INT32_MAX) return false;
+  for (int32_t c = 0; c < ns; ++c) so[c + 1] += so[c];
+  if (part.size() == 1) {
+    offs.swap(part[0]);
+    return true;
+  }
   offs.clear();
-  std::vector<int32_t> d;
-  for (int32_t c = 0; c < ns; ++c) {
-    slice_offsets(n, rp, ci, c, d);
-    offs.insert(offs.end(), d.begin(), d.end());
-    so[c + 1] = (int32_t)offs.size();
+  offs.reserve(so[ns]);
+  for (const auto &v : part) offs.insert(offs.end(), v.begin(), v.end());
+  return true;
+}
+
+void store_value(int dt, double x, uint8_t *p) {
+  const auto put = [&](auto u) { std::memcpy(p, &u, sizeof u); };
+  switch (dt) {
+    case pcgk::F64: put(x); break;
+    case pcgk::F32: put((float)x); break;
+    case pcgk::BF16: put(to_bf16_bits(x)); break;
+    default: put(to_f16_bits(x)); break;
   }
 }
 
-void sdia_bytes(int32_t n, const int32_t *rp, const int32_t *ci, const uint8_t *in, size_t esz,
-                const std::vector<int32_t> &so, const std::vector<int32_t> &offs, std::vector<uint8_t> &out) {
-  const int32_t ns = (int32_t)so.size() - 1;
-  out.assign((size_t)so[ns] * kSlice * esz, 0);
-  for (int32_t r = 0; r < n; ++r) {
-    const int32_t c = r / kSlice, l = r % kSlice;
+namespace {
+// One storage type's loop over slices [c0, c1).
+template <int DT>
+void place_slices(int32_t n, const int32_t *rp, const int32_t *ci, const double *v, double scale,
+                  const std::vector<int32_t> &so, const std::vector<int32_t> &offs, uint8_t *out, int64_t c0,
+                  int64_t c1) {
+  const size_t esz = pcgk::dtype_size(DT);
+  std::memset(out + (size_t)so[c0] * kSlice * esz, 0, (size_t)(so[c1] - so[c0]) * kSlice * esz);
+  for (int64_t r = c0 * kSlice; r < std::min<int64_t>(n, c1 * kSlice); ++r) {
+    const int64_t c = r / kSlice, l = r % kSlice;
     int32_t k = so[c];
     for (int32_t q = rp[r]; q < rp[r + 1]; ++q) {  // both ascending: one merge pass
       while (offs[k] != ci[q] - r) ++k;
-      std::memcpy(&out[((size_t)k * kSlice + l) * esz], in + (size_t)q * esz, esz);
+      store_value(DT, v[q] * scale, out + ((size_t)k * kSlice + l) * esz);
     }
   }
+}
+}  // namespace
+
+void sdia_values(int32_t n, const int32_t *rp, const int32_t *ci, const double *v, int dt, double scale,
+                 const std::vector<int32_t> &so, const std::vector<int32_t> &offs, Bytes &out, int threads) {
+  const int32_t ns = (int32_t)so.size() - 1;
+  out.resize(std::max<size_t>((size_t)so[ns] * kSlice * pcgk::dtype_size(dt), 1));
+  parallel_parts(threads, ns, kRowGrain / kSlice, [&](int64_t lo, int64_t hi, int) {
+    switch (dt) {
+      case pcgk::F64: place_slices<pcgk::F64>(n, rp, ci, v, scale, so, offs, out.data(), lo, hi); break;
+      case pcgk::F32: place_slices<pcgk::F32>(n, rp, ci, v, scale, so, offs, out.data(), lo, hi); break;
+      case pcgk::BF16: place_slices<pcgk::BF16>(n, rp, ci, v, scale, so, offs, out.data(), lo, hi); break;
+      default: place_slices<pcgk::F16>(n, rp, ci, v, scale, so, offs, out.data(), lo, hi); break;
+    }
+  });
 }
 
 bool is_block3(int32_t n, const int32_t *rp, const int32_t *ci, int64_t *blocks) {
@@ -533,9 +610,10 @@ void bsell_pattern(int32_t n, const int32_t *rp, const int32_t *ci, std::vector<
 }
 
 void bsell_bytes(int32_t n, const int32_t *rp, const uint8_t *in, size_t esz, const std::vector<int32_t> &bo,
-                 std::vector<uint8_t> &out) {
+                 Bytes &out) {
   const int32_t nbr = n / 3, ns = (int32_t)bo.size() - 1;
-  out.assign((size_t)bo[ns] * kBSlice * 9 * esz, 0);
+  out.resize((size_t)bo[ns] * kBSlice * 9 * esz);
+  std::fill(out.begin(), out.end(), uint8_t(0));
   for (int32_t R = 0; R < nbr; ++R) {
     const int32_t c = R / kBSlice, r = R % kBSlice, nbk = (rp[3 * R + 1] - rp[3 * R]) / 3;
     for (int32_t k = 0; k < nbk; ++k)

@@ -2,15 +2,76 @@
 // rounding to the half storage formats, preconditioner construction, and the
 // row-block partition used by the kernels. No GPU calls.
 #pragma once
+#include <algorithm>
 #include <climits>
 #include <cstdint>
+#include <exception>
+#include <memory>
 #include <string>
+#include <thread>
 #include <vector>
 
 namespace pcgh {
 
+// CPUs this process may run on (its affinity mask), at least 1.
+unsigned available_cpus();
+
+// f(lo, hi, part) over [0, n) split into equal parts on up to `threads` threads
+// (0: available_cpus(), at most 16), at least `grain` items each, so small work
+// stays on the calling thread; parts are numbered in ascending order of their
+// ranges, and part_count gives their number beforehand. A part whose thread cannot be started runs on
+// the calling thread; the first exception of any part is thrown here.
+inline int part_count(int threads, int64_t n, int64_t grain) {
+  const int64_t most = threads > 0 ? threads : (int64_t)std::min(16u, available_cpus());
+  return (int)std::max<int64_t>(1, std::min(most, n / std::max<int64_t>(grain, 1)));
+}
+template <typename F>
+void parallel_parts(int threads, int64_t n, int64_t grain, F f) {
+  const int np = part_count(threads, n, grain);
+  std::vector<std::exception_ptr> err(np);
+  auto run = [&](int t) {
+    try {
+      f(n * t / np, n * (t + 1) / np, t);
+    } catch (...) {
+      err[t] = std::current_exception();
+    }
+  };
+  std::vector<std::thread> th;
+  th.reserve(np);
+  int started = 1;  // part 0 runs here
+  try {
+    for (; started < np; ++started) th.emplace_back(run, started);
+  } catch (...) {  // no more threads: the rest runs here
+  }
+  run(0);
+  for (int t = started; t < np; ++t) run(t);
+  for (auto &t : th) t.join();
+  for (auto &e : err)
+    if (e) std::rethrow_exception(e);
+}
+
+// Bytes whose resize leaves new elements uninitialised: a layout's values are
+// cleared by the threads that fill them.
+template <typename T>
+struct RawAllocator : std::allocator<T> {
+  template <typename U>
+  struct rebind {
+    using other = RawAllocator<U>;
+  };
+  template <typename U>
+  void construct(U *p) {
+    ::new ((void *)p) U;
+  }
+  template <typename U, typename... A>
+  void construct(U *p, A &&...a) {
+    ::new ((void *)p) U(std::forward<A>(a)...);
+  }
+};
+using Bytes = std::vector<uint8_t, RawAllocator<uint8_t>>;
+
 // PCG_OK or PCG_EINVAL (with a reason in *why when given).
-int validate_csr(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *ci, int require_diag, std::string *why);
+int validate_csr(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *ci, int require_diag, std::string *why,
+                 int threads = 1);
 
 // CSR of the transpose of an n x n matrix (stable: rows of the transpose list
 // the original rows in ascending order).
@@ -24,9 +85,6 @@ uint16_t to_f16_bits(double v);
 
 // Nonzeros of G for a preconditioner kind on A's pattern (-1: unknown kind).
 int64_t g_nnz(int kind, int32_t n, const int32_t *rp, const int32_t *ci);
-
-// CPUs this process may run on (its affinity mask), at least 1.
-unsigned available_cpus();
 
 // G (CSR) for a preconditioner kind built from A (seed: PCG_G_SEEDED). The
 // FSAI rows are built on `threads` threads (0: available_cpus(), at most 32;
@@ -57,7 +115,7 @@ void sell_columns(int32_t n, const int32_t *rp, const int32_t *ci, const std::ve
 // Elements of `esz` bytes in CSR order (`in`) moved to sliced order; padding
 // is all-zero bytes (+0 in every floating-point format).
 void sell_bytes(int32_t n, const int32_t *rp, const uint8_t *in, size_t esz, const std::vector<int32_t> &so,
-                std::vector<uint8_t> &out);
+                Bytes &out);
 
 // Sliced diagonal layout (SDIA): slices of kSlice rows as in sliced ELL, but
 // the column of an entry is stored once per slice as its offset from the
@@ -73,14 +131,19 @@ void sell_bytes(int32_t n, const int32_t *rp, const uint8_t *in, size_t esz, con
 int64_t sdia_entries(int32_t n, const int32_t *rp, const int32_t *ci, int64_t stop = INT64_MAX);
 
 // Slice offsets into offs (nslice + 1, in units of listed offsets) and the
-// listed offsets, slice by slice.
-void sdia_pattern(int32_t n, const int32_t *rp, const int32_t *ci, std::vector<int32_t> &so,
-                  std::vector<int32_t> &offs);
+// listed offsets, slice by slice; false as soon as more than `cap` values
+// would be stored (so and offs are then unspecified).
+bool sdia_pattern(int32_t n, const int32_t *rp, const int32_t *ci, int64_t cap, std::vector<int32_t> &so,
+                  std::vector<int32_t> &offs, int threads);
 
-// Elements of `esz` bytes in CSR order moved to the SDIA order (all other
-// bytes zero).
-void sdia_bytes(int32_t n, const int32_t *rp, const int32_t *ci, const uint8_t *in, size_t esz,
-                const std::vector<int32_t> &so, const std::vector<int32_t> &offs, std::vector<uint8_t> &out);
+// A storage type's conversion of v * scale (dt a pcgk::Dtype) into the bytes
+// at p.
+void store_value(int dt, double v, uint8_t *p);
+
+// The values v (CSR order) times scale in dt, in the SDIA order (zeros where a
+// row has no entry).
+void sdia_values(int32_t n, const int32_t *rp, const int32_t *ci, const double *v, int dt, double scale,
+                 const std::vector<int32_t> &so, const std::vector<int32_t> &offs, Bytes &out, int threads);
 
 // Sliced 3x3-block layout: the matrix is exactly 3x3-blocked when n % 3 == 0
 // and rows 3R, 3R+1, 3R+2 store the same columns, all in complete groups
@@ -108,7 +171,7 @@ void bsell_pattern(int32_t n, const int32_t *rp, const int32_t *ci, std::vector<
 // Elements of `esz` bytes in CSR order moved to the sliced block order
 // (padding all-zero bytes).
 void bsell_bytes(int32_t n, const int32_t *rp, const uint8_t *in, size_t esz, const std::vector<int32_t> &bo,
-                 std::vector<uint8_t> &out);
+                 Bytes &out);
 
 // Algorithmic bytes of one PCG iteration (11 vector streams).
 double bytes_per_iter(int32_t n, int64_t a, int64_t g, int adt, int gdt, int vdt);

@@ -237,7 +237,7 @@ struct HostMat {
   int64_t nnz = 0;           // nonzeros of the matrix (padding excluded)
   std::vector<int32_t> rp;   // CSR row pointers (FMT_CSR only)
   std::vector<int32_t> ci;   // columns in storage order
-  std::vector<uint8_t> val;  // values in dt, in storage order (empty: written on the device)
+  pcgh::Bytes val;           // values in dt, in storage order (empty: written on the device)
   std::vector<int32_t> blk;  // row-block pairs (FMT_CSR) or slice offsets (sliced layouts)
   std::vector<int16_t> ci16; // FMT_SELL with idx16: column - row of each stored entry (ci then empty)
   int64_t stored = 0;        // stored indices (padding included)
@@ -281,7 +281,7 @@ struct APart {
   HostMat A;
   // refinement view: FP64 values of A on A's pattern (shared on the device),
   // with its own row blocks in the CSR layout
-  std::vector<uint8_t> sliced64;  // sliced FP64 values (FMT_SELL)
+  pcgh::Bytes sliced64;           // sliced FP64 values (FMT_SELL)
   const double *val64 = nullptr;  // CSR-ordered FP64 values (FMT_CSR, borrowed)
   std::vector<int32_t> blk64;
   int32_t nunits64 = 0, grid64 = 8, gB = 8;
@@ -329,17 +329,10 @@ int norm_grid(int32_t n) {
   return (int)((g + 7) & ~int64_t(7));
 }
 
-void cast_values(const double *v, int64_t nnz, int dt, double scale, std::vector<uint8_t> &out) {
-  out.resize(pcgk::dtype_size(dt) * (size_t)std::max<int64_t>(nnz, 1));
-  for (int64_t k = 0; k < nnz; ++k) {
-    const double x = v[k] * scale;
-    switch (dt) {
-      case pcgk::F64: ((double *)out.data())[k] = x; break;
-      case pcgk::F32: ((float *)out.data())[k] = (float)x; break;
-      case pcgk::BF16: ((uint16_t *)out.data())[k] = pcgh::to_bf16_bits(x); break;
-      default: ((uint16_t *)out.data())[k] = pcgh::to_f16_bits(x); break;
-    }
-  }
+void cast_values(const double *v, int64_t nnz, int dt, double scale, pcgh::Bytes &out) {
+  const size_t esz = pcgk::dtype_size(dt);
+  out.resize(esz * (size_t)std::max<int64_t>(nnz, 1));
+  for (int64_t k = 0; k < nnz; ++k) pcgh::store_value(dt, v[k] * scale, out.data() + (size_t)k * esz);
 }
 
 // Layout choice (pcg_config.layout): the sliced layout when its padding stays
@@ -386,12 +379,11 @@ bool use_bsr3(int layout, int32_t n, const int32_t *rp, const int32_t *ci) {
 // The slice offsets and listed offsets of the sliced diagonal layout into M
 // (blk, ci), when the layout is allowed and fits. Irregular patterns are
 // turned down after their first slices (the stored count only grows).
-bool sdia_layout(int layout, int32_t n, const int32_t *rp, const int32_t *ci, HostMat &M) {
+bool sdia_layout(int layout, int32_t n, const int32_t *rp, const int32_t *ci, HostMat &M, int threads) {
   if (n <= 0 || !sdia_allowed(layout)) return false;
   const int64_t nnz = rp[n];
   const int64_t cap = layout == PCG_LAYOUT_SDIA ? 2 * nnz + pcgh::kSlice : nnz + nnz / 8;
-  if (pcgh::sdia_entries(n, rp, ci, cap) > cap) return false;
-  pcgh::sdia_pattern(n, rp, ci, M.blk, M.ci);
+  if (!pcgh::sdia_pattern(n, rp, ci, cap, M.blk, M.ci, threads)) return false;
   return sdia_fits(layout, nnz, (int64_t)M.ci.size() * pcgh::kSlice);
 }
 
@@ -399,7 +391,7 @@ bool sdia_layout(int layout, int32_t n, const int32_t *rp, const int32_t *ci, Ho
 // products in vector type vdt. `blocks`: the 3x3-block layout may be used.
 // Preference: 3x3 blocks, sliced diagonals, sliced ELL, CSR row blocks.
 void make_pattern(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, const int32_t *ci, int dt, int vdt,
-                  HostMat &M, bool blocks = false) {
+                  HostMat &M, int threads, bool blocks = false) {
   M.n = n;
   M.nnz = rp[n];
   M.dt = dt;
@@ -415,7 +407,7 @@ void make_pattern(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, 
     M.nunits = (int32_t)M.blk.size() - 1;
     const int32_t rounds = (M.nunits + pcgk::kBlock / 64 - 1) / (pcgk::kBlock / 64);
     M.grid = grid_for(cus, cfg.grid_mult, rounds);
-  } else if (sdia_layout(cfg.layout, n, rp, ci, M)) {
+  } else if (sdia_layout(cfg.layout, n, rp, ci, M, threads)) {
     M.fmt = pcgk::FMT_SDIA;
     M.rp.clear();
     M.nunits = (int32_t)M.blk.size() - 1;
@@ -496,7 +488,7 @@ void block_cover(int32_t n, const int32_t *rp, const int32_t *ci, std::vector<in
 // of a pattern that is not exactly blocked (explicit zeros pad it), when the
 // cover adds at most 1/8 of the nonzeros (2x with the block layout forced).
 void make_mat(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, const int32_t *ci, const double *v,
-              int dt, double scale, int vdt, HostMat &M, int blocks = 0) {
+              int dt, double scale, int vdt, HostMat &M, int threads, int blocks = 0) {
   if (blocks == 2 && n > 0 && n % 3 == 0 && (cfg.layout == PCG_LAYOUT_AUTO || cfg.layout == PCG_LAYOUT_BSR3) &&
       !pcgh::is_block3(n, rp, ci, nullptr)) {
     const int64_t nnz = rp[n], x = block_cover_size(n, rp, ci);
@@ -507,20 +499,22 @@ void make_mat(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, cons
       block_cover(n, rp, ci, xrp, xci, src);
       std::vector<double> xv(x);
       for (int64_t k = 0; k < x; ++k) xv[k] = src[k] >= 0 ? v[src[k]] : 0.0;
-      make_mat(cfg, cus, n, xrp.data(), xci.data(), xv.data(), dt, scale, vdt, M, 1);
+      make_mat(cfg, cus, n, xrp.data(), xci.data(), xv.data(), dt, scale, vdt, M, threads, 1);
       if (M.fmt == pcgk::FMT_BSR3) {
         M.nnz = nnz;  // the matrix's own nonzeros (explicit zeros are padding)
         return;
       }
     }
   }
-  make_pattern(cfg, cus, n, rp, ci, dt, vdt, M, blocks != 0);
-  std::vector<uint8_t> csr_val;
+  make_pattern(cfg, cus, n, rp, ci, dt, vdt, M, threads, blocks != 0);
+  if (M.fmt == pcgk::FMT_SDIA) {
+    pcgh::sdia_values(n, rp, ci, v, dt, scale, M.blk, M.ci, M.val, threads);
+    return;
+  }
+  pcgh::Bytes csr_val;
   cast_values(v, M.nnz, dt, scale, csr_val);
   if (M.fmt == pcgk::FMT_BSR3)
     pcgh::bsell_bytes(n, rp, csr_val.data(), pcgk::dtype_size(dt), M.blk, M.val);
-  else if (M.fmt == pcgk::FMT_SDIA)
-    pcgh::sdia_bytes(n, rp, ci, csr_val.data(), pcgk::dtype_size(dt), M.blk, M.ci, M.val);
   else if (M.fmt == pcgk::FMT_SELL)
     pcgh::sell_bytes(n, rp, csr_val.data(), pcgk::dtype_size(dt), M.blk, M.val);
   else
@@ -528,14 +522,14 @@ void make_mat(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, cons
 }
 
 void prep_a(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, const int32_t *ci, const double *v,
-            bool staging, APart &P) {
+            bool staging, APart &P, int threads) {
   P.n = n;
   P.nnz = rp[n];
   P.adt = cfg.a_dtype;
   P.vdt = cfg.vec_dtype;
   P.refine = cfg.refine != 0;
   P.staging = staging;
-  make_mat(cfg, cus, n, rp, ci, v, P.adt, 1.0, P.vdt, P.A, 1);
+  make_mat(cfg, cus, n, rp, ci, v, P.adt, 1.0, P.vdt, P.A, threads, 1);
   P.gB = norm_grid(n);
   size_t b64 = 0;
   if (P.refine) {
@@ -543,7 +537,7 @@ void prep_a(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, const 
       if (P.A.fmt == pcgk::FMT_BSR3)
         pcgh::bsell_bytes(n, rp, (const uint8_t *)v, 8, P.A.blk, P.sliced64);
       else if (P.A.fmt == pcgk::FMT_SDIA)
-        pcgh::sdia_bytes(n, rp, ci, (const uint8_t *)v, 8, P.A.blk, P.A.ci, P.sliced64);
+        pcgh::sdia_values(n, rp, ci, v, pcgk::F64, 1.0, P.A.blk, P.A.ci, P.sliced64, threads);
       else
         pcgh::sell_bytes(n, rp, (const uint8_t *)v, 8, P.A.blk, P.sliced64);
       P.nunits64 = P.A.nunits;
@@ -568,7 +562,7 @@ void prep_a(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, const 
 }
 
 void prep_g(const pcg_config &cfg, int cus, int32_t n, std::vector<int32_t> &grp, std::vector<int32_t> &gci,
-            std::vector<double> &gv, GPart &P) {
+            std::vector<double> &gv, GPart &P, int threads) {
   P.n = n;
   P.nnz = (int64_t)gci.size();
   P.gdt = cfg.g_dtype;
@@ -588,8 +582,8 @@ void prep_g(const pcg_config &cfg, int cus, int32_t n, std::vector<int32_t> &grp
       P.scale = std::ldexp(1.0, 14 - e);  // max |G| scaled into [2^13, 2^14)
     }
   }
-  make_mat(cfg, cus, n, grp.data(), gci.data(), gv.data(), P.gdt, P.scale, P.vdt, P.G, 2);
-  make_mat(cfg, cus, n, trp.data(), tci.data(), tv.data(), P.gdt, P.scale, P.vdt, P.GT, 2);
+  make_mat(cfg, cus, n, grp.data(), gci.data(), gv.data(), P.gdt, P.scale, P.vdt, P.G, threads, 2);
+  make_mat(cfg, cus, n, trp.data(), tci.data(), tv.data(), P.gdt, P.scale, P.vdt, P.GT, threads, 2);
   P.bytes = P.G.bytes() + P.GT.bytes() + align_up(16 * pcgk::kAccWords * (size_t)P.GT.grid);
 }
 
@@ -1701,8 +1695,8 @@ bool prep_fsai_pattern(const pcg_config &cfg, int cus, Req &R) {
   P.nnz = lrp[n];
   P.gdt = cfg.g_dtype;
   P.vdt = cfg.vec_dtype;
-  make_pattern(cfg, cus, n, grp.data(), gci.data(), P.gdt, P.vdt, P.G);
-  make_pattern(cfg, cus, n, lrp.data(), lci.data(), P.gdt, P.vdt, P.GT);
+  make_pattern(cfg, cus, n, grp.data(), gci.data(), P.gdt, P.vdt, P.G, 1);
+  make_pattern(cfg, cus, n, lrp.data(), lci.data(), P.gdt, P.vdt, P.GT, 1);
   P.bytes = P.G.bytes() + P.GT.bytes() + align_up(16 * pcgk::kAccWords * (size_t)P.GT.grid);
   R.fs_dpos.swap(dpos);
   R.fs_lrp.swap(lrp);
@@ -1767,7 +1761,7 @@ void prep_request(const pcg_config &cfg, int cus, PinnedArena *arena, Req &R) {
 
 void prep_parts(const pcg_config &cfg, int cus, Req &R) {
   R.ap = APart{};
-  prep_a(cfg, cus, R.n, R.a_rp.data(), R.a_ci.data(), R.a_val.data(), false, R.ap);
+  prep_a(cfg, cus, R.n, R.a_rp.data(), R.a_ci.data(), R.a_val.data(), false, R.ap, 1);
   if (!R.g_given && R.g_kind == PCG_G_FSAI && cfg.g_device && cfg.g_dtype != PCG_F16 &&
       prep_fsai_pattern(cfg, cus, R)) {
     R.bytes = R.ap.bytes + R.gp.bytes;
@@ -1789,7 +1783,7 @@ void prep_parts(const pcg_config &cfg, int cus, Req &R) {
     }
   }
   R.gp = GPart{};
-  prep_g(cfg, cus, R.n, grp, gci, gv, R.gp);
+  prep_g(cfg, cus, R.n, grp, gci, gv, R.gp, 1);
   R.bytes = R.ap.bytes + R.gp.bytes;
   R.prep_rc = PCG_OK;
 }
@@ -2726,7 +2720,7 @@ void pcg_destroy(pcg_ctx *ctx) {
 static int place_single_a(pcg_ctx *ctx) {
   const int32_t n = (int32_t)ctx->a_rp.size() - 1;
   APart P;
-  prep_a(eff_cfg(ctx, false), ctx->cus, n, ctx->a_rp.data(), ctx->a_ci.data(), ctx->a_val.data(), true, P);
+  prep_a(eff_cfg(ctx, false), ctx->cus, n, ctx->a_rp.data(), ctx->a_ci.data(), ctx->a_val.data(), true, P, 0);
   void *blk = nullptr;
   if (ctx->da.get(&blk, P.bytes) != hipSuccess) {
     (void)hipGetLastError();
@@ -2772,7 +2766,7 @@ int pcg_set_matrix(pcg_ctx *ctx, int32_t n, int64_t nnz, const int32_t *rowptr, 
     hci.assign(col, col + nnz);
     hv.assign(val, val + nnz);
   }
-  int rc = pcgh::validate_csr(n, nnz, hrp.data(), hci.data(), 1, &ctx->err);
+  int rc = pcgh::validate_csr(n, nnz, hrp.data(), hci.data(), 1, &ctx->err, 0);
   if (rc) return rc;
   drop_graphs(ctx);
   free_set(ctx, ctx->set_main);
@@ -2810,7 +2804,7 @@ static int set_g_from_host(pcg_ctx *ctx, std::vector<int32_t> &grp, std::vector<
   ctx->g_val = gv;
   ctx->g_from_device = false;
   GPart P;
-  prep_g(eff_cfg(ctx, true), ctx->cus, ctx->single.n, grp, gci, gv, P);
+  prep_g(eff_cfg(ctx, true), ctx->cus, ctx->single.n, grp, gci, gv, P, 0);
   void *blk = nullptr;
   if (ctx->da.get(&blk, P.bytes) != hipSuccess) {
     (void)hipGetLastError();
@@ -2861,7 +2855,7 @@ int pcg_set_precond(pcg_ctx *ctx, int32_t n, int64_t nnz, const int32_t *rowptr,
     hci.assign(col, col + nnz);
     hv.assign(val, val + nnz);
   }
-  int rc = pcgh::validate_csr(n, nnz, hrp.data(), hci.data(), 0, &ctx->err);
+  int rc = pcgh::validate_csr(n, nnz, hrp.data(), hci.data(), 0, &ctx->err, 0);
   if (rc) return rc;
   rc = set_g_from_host(ctx, hrp, hci, hv);
   if (!rc && ctx->cfg.autotune) rc = pcg_autotune(ctx, 20, nullptr);
@@ -2878,27 +2872,39 @@ static int build_fsai_device(pcg_ctx *ctx) {
   const int32_t *rp = ctx->a_rp.data(), *ci = ctx->a_ci.data();
   const double *v = ctx->a_val.data();
   std::vector<int32_t> dpos(n), lrp(n + 1, 0), lci, grp(n + 1, 0), gci;
+  constexpr int64_t grain = 16384;  // rows per thread at least
+  std::atomic<bool> missing{false};
+  pcgh::parallel_parts(0, n, grain, [&](int64_t lo, int64_t hi, int) {
+    for (int64_t i = lo; i < hi; ++i) {
+      const int32_t *p = std::lower_bound(ci + rp[i], ci + rp[i + 1], (int32_t)i);
+      if (p == ci + rp[i + 1] || *p != i) {
+        missing = true;
+        return;
+      }
+      dpos[i] = (int32_t)(p - ci);
+      lrp[i + 1] = dpos[i] - rp[i] + 1;
+      grp[i + 1] = rp[i + 1] - dpos[i];
+    }
+  });
+  if (missing) {
+    ctx->err = "pcg_build_precond: FSAI needs a stored diagonal in every row";
+    return PCG_EINVAL;
+  }
   int32_t mmax = 0;
   for (int32_t i = 0; i < n; ++i) {
-    int32_t d = -1;
-    for (int32_t k = rp[i]; k < rp[i + 1]; ++k)
-      if (ci[k] == i) d = k;
-    if (d < 0) {
-      ctx->err = "pcg_build_precond: FSAI needs a stored diagonal in every row";
-      return PCG_EINVAL;
-    }
-    dpos[i] = d;
-    mmax = std::max(mmax, d - rp[i] + 1);
-    lrp[i + 1] = lrp[i] + (d - rp[i] + 1);
-    grp[i + 1] = grp[i] + (rp[i + 1] - d);
+    mmax = std::max(mmax, lrp[i + 1]);
+    lrp[i + 1] += lrp[i];
+    grp[i + 1] += grp[i];
   }
   if (mmax > pcgk::kFsaiMaxRow || lrp[n] != grp[n]) return 1;  // long rows or unsymmetric counts
   lci.resize(lrp[n]);
   gci.resize(grp[n]);
-  for (int32_t i = 0; i < n; ++i) {
-    std::copy(ci + rp[i], ci + dpos[i] + 1, lci.begin() + lrp[i]);
-    std::copy(ci + dpos[i], ci + rp[i + 1], gci.begin() + grp[i]);
-  }
+  pcgh::parallel_parts(0, n, grain, [&](int64_t lo, int64_t hi, int) {
+    for (int64_t i = lo; i < hi; ++i) {
+      std::copy(ci + rp[i], ci + dpos[i] + 1, lci.begin() + lrp[i]);
+      std::copy(ci + dpos[i], ci + rp[i + 1], gci.begin() + grp[i]);
+    }
+  });
   drop_graphs(ctx);
   if (S.blkG) {
     ctx->da.put(S.blkG);
@@ -2911,8 +2917,8 @@ static int build_fsai_device(pcg_ctx *ctx) {
   P.gdt = ctx->cfg.g_dtype;
   P.vdt = ctx->cfg.vec_dtype;
   const pcg_config gcfg = eff_cfg(ctx, true);
-  make_pattern(gcfg, ctx->cus, n, grp.data(), gci.data(), P.gdt, P.vdt, P.G);
-  make_pattern(gcfg, ctx->cus, n, lrp.data(), lci.data(), P.gdt, P.vdt, P.GT);
+  make_pattern(gcfg, ctx->cus, n, grp.data(), gci.data(), P.gdt, P.vdt, P.G, 0);
+  make_pattern(gcfg, ctx->cus, n, lrp.data(), lci.data(), P.gdt, P.vdt, P.GT, 0);
   P.bytes = P.G.bytes() + P.GT.bytes() + align_up(16 * pcgk::kAccWords * (size_t)P.GT.grid);
   // temporaries: A (CSR, FP64), dpos, lrp, G_L's values, flags, partial maxima
   const int64_t nnz = rp[n], nl = lrp[n];
