@@ -944,6 +944,16 @@ __device__ __forceinline__ Work work_of(const SysDev *__restrict__ dir, const in
   return w;
 }
 
+// Tells the host how far a solve has come: 2 iter + done into a word of
+// page-locked host memory, from the thread that publishes the state. A copy of
+// the state and an event after every graph of ten iterations took 18 us of the
+// stream (gaps of 8.5 and 5.6 us around a 4 us copy), 1.8 us per iteration.
+__device__ __forceinline__ void report_progress(uint64_t *report, int32_t iter, int32_t done) {
+  if (report)
+    __hip_atomic_store(report, 2 * (uint64_t)(uint32_t)iter + (done ? 1 : 0), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Rows [l n / G, (l+1) n / G) of a system: local workgroup l's share of
 // elementwise work over G workgroups.
 __device__ __forceinline__ void ew_rows(int n, int l, int G, int64_t &i0, int64_t &i1) {

@@ -286,7 +286,7 @@ __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_dia_GT(DiaOp B, Dia
 // others read st[1] only. At 128^3 FP64 (151 MB): 24.4 -> 22.3 us.
 template <typename TV, typename TG, int ND, int R, bool NT, bool HAS_EPS>
 __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_dia_G(DiaOp B, DiaVecs v, int par, int gridGT,
-                                                                   int grid) {
+                                                                   int grid, uint64_t *report) {
   __shared__ Acc sh[4 * (kBlock / 64)];
   const int l = blockIdx.x, n = v.n, lane = threadIdx.x & 63;
   GLOBAL State *st = gl(v.st);
@@ -380,6 +380,7 @@ __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_dia_G(DiaOp B, DiaV
       }
     }
     st_state(st, o);
+    report_progress(report, o.iter, o.done);
   }
   if (!go && !was_done) {  // stopped: x_{i+1} only
     int64_t i0, i1r;
@@ -499,27 +500,27 @@ hipError_t launch_dia_GT(const Types &ty, const DiaOp &B, const DiaVecs &v, int 
 
 template <typename TV, typename TG, int ND, int R>
 static hipError_t launch_g(const DiaOp &B, const DiaVecs &v, bool has_eps, int par, int gridGT, int grid,
-                           hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+                           hipStream_t s, hipEvent_t e0, hipEvent_t e1, uint64_t *report) {
   if (has_eps) {
     if (B.temporal)
-      PCG_DIA_LAUNCH((k_dia_G<TV, TG, ND, R, false, true>), grid, B, v, par, gridGT, grid);
+      PCG_DIA_LAUNCH((k_dia_G<TV, TG, ND, R, false, true>), grid, B, v, par, gridGT, grid, report);
     else
-      PCG_DIA_LAUNCH((k_dia_G<TV, TG, ND, R, true, true>), grid, B, v, par, gridGT, grid);
+      PCG_DIA_LAUNCH((k_dia_G<TV, TG, ND, R, true, true>), grid, B, v, par, gridGT, grid, report);
   } else {
     if (B.temporal)
-      PCG_DIA_LAUNCH((k_dia_G<TV, TG, ND, R, false, false>), grid, B, v, par, gridGT, grid);
+      PCG_DIA_LAUNCH((k_dia_G<TV, TG, ND, R, false, false>), grid, B, v, par, gridGT, grid, report);
     else
-      PCG_DIA_LAUNCH((k_dia_G<TV, TG, ND, R, true, false>), grid, B, v, par, gridGT, grid);
+      PCG_DIA_LAUNCH((k_dia_G<TV, TG, ND, R, true, false>), grid, B, v, par, gridGT, grid, report);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_dia_G(const Types &ty, const DiaOp &B, const DiaVecs &v, bool has_eps, int par, int gridGT, int grid,
-                        hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+                        hipStream_t s, hipEvent_t e0, hipEvent_t e1, uint64_t *report) {
   PCG_DIA_ND(B.nd, ND, PCG_DIA_G(ty.g, TG, {
-    if (ty.vec == F64) return launch_g<double, TG, ND, kDiaR64>(B, v, has_eps, par, gridGT, grid, s, e0, e1);
+    if (ty.vec == F64) return launch_g<double, TG, ND, kDiaR64>(B, v, has_eps, par, gridGT, grid, s, e0, e1, report);
     if constexpr (!std::is_same_v<TG, double>)
-      return launch_g<float, TG, ND, kDiaR32>(B, v, has_eps, par, gridGT, grid, s, e0, e1);
+      return launch_g<float, TG, ND, kDiaR32>(B, v, has_eps, par, gridGT, grid, s, e0, e1, report);
   }));
   return hipErrorInvalidValue;
 }

@@ -226,8 +226,10 @@ hipError_t launch_iter_GT(const Types &ty, const LaunchSet &L, int mode, hipStre
 // publishes st[0]; then, unless stopped, d_{i+1} = (G t + eps r) + beta d_i
 // (beta = 0 in mode 2), and x += alpha_i d_i (not in mode 2; also when the
 // system stops at this iteration). Reads st[1] only.
+// report (page-locked host memory, or null): 2 iter + done of the published
+// state (launches of a single system only).
 hipError_t launch_iter_G(const Types &ty, const LaunchSet &L, bool has_eps, int mode, hipStream_t s,
-                         hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+                         hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr, uint64_t *report = nullptr);
 
 // The three kernels of an ordinary iteration (mode 0) over stencil storage;
 // par: the parity of the iteration index i (it selects the r and d slots).
@@ -238,7 +240,7 @@ hipError_t launch_dia_A(const Types &ty, const DiaOp &A, const DiaVecs &v, int p
 hipError_t launch_dia_GT(const Types &ty, const DiaOp &B, const DiaVecs &v, int par, int gridA, int grid,
                          hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_dia_G(const Types &ty, const DiaOp &B, const DiaVecs &v, bool has_eps, int par, int gridGT, int grid,
-                        hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+                        hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr, uint64_t *report = nullptr);
 
 // Fills o (val allocated, ld, nd, dist set) from M, placed in sliced
 // diagonals. flag (device, cleared by the caller) set: flag[0] = 1 if M's

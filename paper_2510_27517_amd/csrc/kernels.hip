@@ -208,7 +208,8 @@ __global__ __launch_bounds__(kBlock) PCG_GT_OCCUPANCY void k_iter_GT(const SysDe
 
 template <typename TV, typename TG, bool HAS_EPS>
 __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev *__restrict__ dir, const int2 *__restrict__ map, SysDev one,
-                                                   int mode) {
+                                                   int mode,
+                                                   uint64_t *report) {
   __shared__ TV lds[kLdsBytes / sizeof(TV)];
   __shared__ Acc sh[4 * (kBlock / 64)];
   const Work wk = work_of(dir, map, one);
@@ -221,7 +222,11 @@ __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev 
   Acc va[2];
   load_partials<2>(gl(D.prt), D.GT.grid, va);  // in flight while the state is read
   if (S.done) {  // stopped earlier, or the G^T-kernel flagged a breakdown
-    if (l == 0 && threadIdx.x == 0) st_state(st, ld_state(&S));
+    if (l == 0 && threadIdx.x == 0) {
+      const State o = ld_state(&S);
+      st_state(st, o);
+      report_progress(report, o.iter, o.done);
+    }
     return;
   }
   const int it = S.iter;
@@ -335,6 +340,7 @@ __global__ __launch_bounds__(kBlock) PCG_G_OCCUPANCY void k_iter_G(const SysDev 
       o.done = 1;
     }
     st_state(st, o);
+    report_progress(report, o.iter, o.done);
   }
   if (!go && upd) {  // stopped: x_{i+1} only
     int64_t i0, i1r;
@@ -893,14 +899,14 @@ hipError_t launch_iter_GT(const Types &ty, const LaunchSet &L, int mode, hipStre
 }
 
 hipError_t launch_iter_G(const Types &ty, const LaunchSet &L, bool has_eps, int mode, hipStream_t s, hipEvent_t e0,
-                         hipEvent_t e1) {
+                         hipEvent_t e1, uint64_t *report) {
   if (L.nG == 0) return hipSuccess;
   PCG_ONE(L.mapG);
   PCG_DISPATCH_V(ty.vec, TV, PCG_DISPATCH_G(ty.g, TG, {
     if (has_eps)
-      PCG_LAUNCH((k_iter_G<TV, TG, true>), L.nG, s, e0, e1, L.dir, map, one, mode);
+      PCG_LAUNCH((k_iter_G<TV, TG, true>), L.nG, s, e0, e1, L.dir, map, one, mode, report);
     else
-      PCG_LAUNCH((k_iter_G<TV, TG, false>), L.nG, s, e0, e1, L.dir, map, one, mode);
+      PCG_LAUNCH((k_iter_G<TV, TG, false>), L.nG, s, e0, e1, L.dir, map, one, mode, report);
   }));
   return hipGetLastError();
 }

@@ -1200,8 +1200,9 @@ int single_sets(pcg_ctx *ctx) {
 
 // Iteration `it` (its parity selects the r and d slots; the general kernels
 // read it from the state). ev: six events around the three kernels, or null.
+// report: where the G-kernel tells the host how far the solve is, or null.
 void enqueue_iteration(pcg_ctx *ctx, const Types &ty, const LaunchSet &L, int it, bool replace, double eps,
-                       hipError_t &e, const hipEvent_t *ev = nullptr) {
+                       hipError_t &e, const hipEvent_t *ev = nullptr, uint64_t *report = nullptr) {
   auto chain = [&](hipError_t x) {
     if (e == hipSuccess) e = x;
   };
@@ -1226,9 +1227,9 @@ void enqueue_iteration(pcg_ctx *ctx, const Types &ty, const LaunchSet &L, int it
     chain(pcgk::launch_iter_GT(ty, L, 0, s, at(2), at(3)));
   }
   if (L.diaG.nd)
-    chain(pcgk::launch_dia_G(ty, L.diaG, v, eps != 0.0, par, L.nGT, L.nG, s, at(4), at(5)));
+    chain(pcgk::launch_dia_G(ty, L.diaG, v, eps != 0.0, par, L.nGT, L.nG, s, at(4), at(5), report));
   else
-    chain(pcgk::launch_iter_G(ty, L, eps != 0.0, replace ? 1 : 0, s, at(4), at(5)));
+    chain(pcgk::launch_iter_G(ty, L, eps != 0.0, replace ? 1 : 0, s, at(4), at(5), report));
 }
 
 // What a single-system PCG runs on: the kernels' types, the launch set, the
@@ -1243,7 +1244,8 @@ struct Core {
 
 Core main_core(pcg_ctx *ctx) { return Core{ctx->ty, &ctx->set_main.L, &ctx->single.dev, kSlotMain, &ctx->graphs}; }
 
-int get_graph(pcg_ctx *ctx, const Core &c, int iters, int base, bool replace_first, double eps, hipGraphExec_t *out) {
+int get_graph(pcg_ctx *ctx, const Core &c, int iters, int base, bool replace_first, double eps, uint64_t *report,
+              hipGraphExec_t *out) {
   const int par = base & 1, key = iters * 4 + par * 2 + (replace_first ? 1 : 0);
   auto it = c.graphs->find(key);
   if (it != c.graphs->end()) {
@@ -1252,7 +1254,9 @@ int get_graph(pcg_ctx *ctx, const Core &c, int iters, int base, bool replace_fir
   }
   HIPCHK(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
-  for (int k = 0; k < iters; ++k) enqueue_iteration(ctx, c.ty, *c.L, par + k, replace_first && k == 0, eps, e);
+  for (int k = 0; k < iters; ++k) 
+    enqueue_iteration(ctx, c.ty, *c.L, par + k, replace_first && k == 0, eps, e, nullptr,
+                      k == iters - 1 ? report : nullptr);
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(ctx->stream, &g);
   HIPCHK(e);
@@ -1289,6 +1293,31 @@ int enqueue_start(pcg_ctx *ctx, const Types &ty, const LaunchSet &L, bool has_ep
 // residual meets tol, check b - A x and restart from it if that fails (the
 // inner solves of refinement skip this: the FP64 outer residual is the check,
 // and an FP32 iterate's true residual has a floor near u32 ||A|| ||x||).
+// Waits until the solve has reported iteration `target` or that it is done (the
+// word is 2 iter + done, 0 before the first report). The wait watches host
+// memory; now and then it asks the stream, which ends it after a device error.
+int await_progress(pcg_ctx *ctx, const uint64_t *report, int target, bool *done) {
+  const volatile uint64_t *w = report;
+  auto ready = [&]() {
+    const uint64_t v = *w;
+    *done = v & 1;
+    return *done || (v != 0 && (int64_t)(v >> 1) >= target);
+  };
+  for (int64_t spin = 1; !ready(); ++spin) {
+    __builtin_ia32_pause();
+    if (spin % 4096) continue;
+    const hipError_t q = hipStreamQuery(ctx->stream);
+    if (q == hipErrorNotReady) continue;
+    HIPCHK(q);
+    if (!ready()) {  // everything launched has ended
+      ctx->err = "pcg_solve: the iteration kernels ended without a report";
+      return PCG_EDEVICE;
+    }
+    break;
+  }
+  return PCG_OK;
+}
+
 // io: the caller's FP64 device vectors, for a solve that use_wgs takes (b and x
 // are then read and written there directly); else b and x are the system's.
 struct DirectIo {
@@ -1368,39 +1397,38 @@ int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out,
     }
     K = a;  // K divides rr: replacement can only fall on a chunk's first iteration
   }
-  State *hst = ctx->h_states + 2 * c.slot;  // two pinned readback buffers
+  State *hst = ctx->h_states + 2 * c.slot;  // page-locked: the final state, and the progress word
+  uint64_t *report = (uint64_t *)&hst[1];
   int base = 0;
   int restarts = 0;
   for (;;) {
-    int inflight = 0, slot_next = 0, slot_wait = 0;
-    bool done = false;
-    while (!done) {
+    // two chunks of iterations are kept in flight; the last iteration of each
+    // reports, and no copy or event stands between two graphs
+    *(volatile uint64_t *)report = 0;
+    int ends[2], inflight = 0, first = 0;
+    for (bool done = false; !done;) {
       while (inflight < 2) {
         const bool rep = rr > 0 && base > 0 && base % rr == 0;
         int len;
         if (K <= 0) {
           hipError_t e = hipSuccess;
-          enqueue_iteration(ctx, ty, L, base, rep, init.eps, e);
+          enqueue_iteration(ctx, ty, L, base, rep, init.eps, e, nullptr, report);
           HIPCHK(e);
           len = 1;
         } else {
           len = (base % K == 0) ? K : 1;
           hipGraphExec_t g;
-          int rc = get_graph(ctx, c, len, base, rep, init.eps, &g);
+          int rc = get_graph(ctx, c, len, base, rep, init.eps, report, &g);
           if (rc) return rc;
           HIPCHK(hipGraphLaunch(g, s));
         }
         base += len;
-        HIPCHK(hipMemcpyAsync(&hst[slot_next], D.st, sizeof(State), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipEventRecord(ctx->ev[slot_next], s));
-        slot_next ^= 1;
-        ++inflight;
+        ends[(first + inflight++) & 1] = base;
       }
-      HIPCHK(hipEventSynchronize(ctx->ev[slot_wait]));
-      const bool d = hst[slot_wait].done != 0;
-      slot_wait ^= 1;
+      int rc = await_progress(ctx, report, ends[first], &done);
+      if (rc) return rc;
+      first ^= 1;
       --inflight;
-      if (d) done = true;
     }
     HIPCHK(hipStreamSynchronize(s));
     State h;
@@ -1411,7 +1439,6 @@ int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out,
       out = CoreOut{};
       return PCG_OK;
     }
-    HIPCHK(pcgk::launch_finalize(ty, L, s));
     HIPCHK(pcgk::launch_resid(ty, L, 0, false, true, false, s));
     HIPCHK(hipMemcpyAsync(&hst[0], D.st, sizeof(State), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
