@@ -1019,10 +1019,14 @@ double placed_bytes(const pcgk::DevCSR &M) {
 // Residency plan of the single system: which matrices are read with ordinary
 // loads, so that they stay in the memory-side cache (cfg.cache_mb, default
 // 256 MB) from one iteration to the next, and which stream past it. All three
-// when the matrices and the 8 iteration vectors fit in 90% of the cache;
-// else the first of A alone, G and G^T together, G alone that fits in 75%
-// (the vectors and the other matrices stream around it); else none. The FP64
-// view of A under refinement always streams.
+// when the matrices and the 8 iteration vectors fit in 105% of the cache: a
+// little over its size most of them still stay (FP64, per iteration, all
+// against A alone: elasticity 40^3, 272 MB, 61.5 us against 67.3; a graph of
+// 800,001, 243 MB, 61.0 against 70.8), far over it nothing does (42^3, 315 MB,
+// 90.9 against 84.2; 44^3 100.7 against 89.0). Else the first of A alone, G and
+// G^T together, G alone that fits in 75% (the vectors and the other matrices
+// stream around it); else none. The FP64 view of A under refinement always
+// streams.
 int residency_plan(const pcg_ctx *ctx) {
   if (ctx->tune.on && ctx->tune.res >= 0) return ctx->tune.res;
   if (ctx->cfg.cache_mb < 0) return 0;
@@ -1030,7 +1034,7 @@ int residency_plan(const pcg_ctx *ctx) {
   const pcgk::SysDev &D = ctx->single.dev;
   const double a = placed_bytes(D.A), g = placed_bytes(D.G) + placed_bytes(D.GT);
   const double v = 8.0 * D.n * (double)pcgk::dtype_size(ctx->ty.vec);
-  if (a + g + v <= 0.9 * cap) return 7;
+  if (a + g + v <= 1.05 * cap) return 7;
   if (a <= 0.75 * cap) return 1;
   if (g <= 0.75 * cap) return 6;
   if (placed_bytes(D.G) <= 0.75 * cap) return 2;
