@@ -20,7 +20,7 @@ ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}"]
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-SOURCES = ["kernels.hip", "wg.hip", "products.hip", "dia.hip", "wgs.hip", "host.cpp", "pcg.cpp"]
+SOURCES = ["kernels.hip", "single.hip", "wg.hip", "products.hip", "dia.hip", "wgs.hip", "host.cpp", "pcg.cpp"]
 
 
 def _run(cmd, verbose):
@@ -51,7 +51,7 @@ def build(verbose: bool = False) -> str:
         _run(cmd, verbose)
         return obj
 
-    with ThreadPoolExecutor(max_workers=6) as pool:  # the sources are independent
+    with ThreadPoolExecutor(max_workers=7) as pool:  # the sources are independent
         objs = list(pool.map(compile_one, SOURCES))
     tmp = LIB + ".tmp"
     _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp, "-lpthread"], verbose)

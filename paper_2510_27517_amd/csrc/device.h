@@ -29,10 +29,6 @@ namespace pcgk {
 // sums of the G^T-kernel: compiled for 4 waves per SIMD like the G^T-kernel.
 #define PCG_G_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4)))
 
-#ifndef PCG_UNROLL
-#define PCG_UNROLL 4
-#endif
-
 struct bf16_t { uint16_t bits; };
 
 // Pointers that come out of the device directory are not known to the
@@ -125,10 +121,12 @@ struct Mat {
   int32_t rpl;
 };
 
-template <typename TM>
+// FMT >= 0: a kernel built for that layout alone, which leaves the others' code
+// and registers out of it.
+template <typename TM, int FMT = -1>
 __device__ __forceinline__ Mat<TM> mat(const DevCSR &m) {
-  return Mat<TM>{gl(m.rp), gl(m.ci), gl((const TM *)m.val), gl(m.blk), m.nblk, m.n, m.fmt, m.idx16, m.temporal,
-                 m.rpl};
+  return Mat<TM>{gl(m.rp),   gl(m.ci), gl((const TM *)m.val), gl(m.blk), m.nblk, m.n, FMT >= 0 ? FMT : m.fmt,
+                 m.idx16, m.temporal, m.rpl};
 }
 
 // Column of stored entry q of `row`: an absolute int32 index, or (sliced
@@ -164,14 +162,50 @@ __device__ __forceinline__ TACC lds_row_sum(const TACC *lds, int a, int e, TACC 
   return sum;
 }
 
+// Products [c0, c1) of a row block into LDS (from c0's slot on). What bounds a
+// block is two dependent memory latencies per round (column, then gather).
+// U > 0: each thread takes U entries a round with all their loads in flight; a
+// round's surplus repeats the last entry (in bounds) and is not stored. U = 0: a
+// plain loop unrolled by four, whose remainder runs one entry after the other.
+// Which is faster depends on the kernel's types: see the kernels' US.
+template <typename TACC, int U, bool NT, typename TM, typename Gather>
+__device__ __forceinline__ void stage_products(const Mat<TM> &M, int c0, int c1, TACC *lds, Gather gather) {
+  if constexpr (U == 0) {
+#pragma unroll 4
+    for (int k = c0 + (int)threadIdx.x; k < c1; k += kBlock)
+      lds[k - c0] = (TACC)ldval<NT>(M.val, k) * gather(ldstream<NT>(M.ci, k));
+  } else {
+    for (int c = c0 + (int)threadIdx.x; c < c1; c += U * kBlock) {
+      int32_t col[U];
+      TACC v[U];
+      decltype(gather(0)) x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(c + u * kBlock, c1 - 1);
+        col[u] = ldstream<NT>(M.ci, k);
+        v[u] = (TACC)ldval<NT>(M.val, k);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = gather(col[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c + u * kBlock < c1) lds[c + u * kBlock - c0] = v[u] * x[u];
+    }
+  }
+}
+
 // One row block: stage products in LDS, sum each row in CSR order. `pre(row)`
 // loads the row's own operands early (overlapping the gathers), `epi(row,
-// sum, pre_values)` consumes the row's sum.
-template <typename TACC, bool NT, typename TM, typename Pre, typename Gather, typename Epi>
-__device__ __forceinline__ void stream_block(const Mat<TM> &M, int b, TACC *lds, Pre pre, Gather gather, Epi epi) {
+// sum, pre_values)` consumes the row's sum. hook: a workgroup step between
+// the products and the first epilogue (it may hold barriers); false ends the
+// walk.
+template <typename TACC, int U, bool NT, typename TM, typename Pre, typename Gather, typename Epi, typename Hook>
+__device__ __forceinline__ bool stream_block(const Mat<TM> &M, int b, TACC *lds, Pre pre, Gather gather, Epi epi,
+                                             Hook hook) {
   constexpr int cap = kLdsBytes / (int)sizeof(TACC);
   const int tid = threadIdx.x;
-  const int r0 = M.blk[2 * b], k0 = M.blk[2 * b + 1], r1 = M.blk[2 * b + 2], k1 = M.blk[2 * b + 3];
+  CONSTANT const int32_t *blk = ro(M.blk) + 2 * b;
+  const int r0 = blk[0], k0 = blk[1], r1 = blk[2], k1 = blk[3];
   if (k1 - k0 <= cap) {
     const int row = r0 + tid;
     const bool has = row < r1;
@@ -182,9 +216,8 @@ __device__ __forceinline__ void stream_block(const Mat<TM> &M, int b, TACC *lds,
       e = M.rp[row + 1] - k0;
       pv = pre(row);
     }
-#pragma unroll PCG_UNROLL
-    for (int k = k0 + tid; k < k1; k += kBlock)
-      lds[k - k0] = (TACC)ldval<NT>(M.val, k) * gather(ldstream<NT>(M.ci, k));
+    stage_products<TACC, U, NT>(M, k0, k1, lds, gather);
+    if (!hook()) return false;
     __syncthreads();
     if (has) epi(row, lds_row_sum(lds, a, e), pv);
     __syncthreads();
@@ -195,15 +228,20 @@ __device__ __forceinline__ void stream_block(const Mat<TM> &M, int b, TACC *lds,
     TACC sum = 0;
     for (int c0 = k0; c0 < k1; c0 += cap) {
       const int c1 = min(c0 + cap, k1);
-      for (int k = c0 + tid; k < c1; k += kBlock)
-        lds[k - c0] = (TACC)ldval<NT>(M.val, k) * gather(ldstream<NT>(M.ci, k));
+      stage_products<TACC, U, NT>(M, c0, c1, lds, gather);
       __syncthreads();
       if (tid == 0) sum = lds_row_sum(lds, 0, c1 - c0, sum);
       __syncthreads();
     }
+    if (!hook()) return false;
     if (tid == 0) epi(r0, sum, pv);
   }
+  return true;
 }
+
+struct NoHook {
+  __device__ __forceinline__ bool operator()() const { return true; }
+};
 
 // This workgroup's row blocks: first, first + stride, ... < end; L is its
 // logical index (the slot of its partial sums). l is the workgroup's index
@@ -305,6 +343,39 @@ __device__ __forceinline__ void sell_rows(const Mat<TM> &M, int l, int G, Pre pr
                              : slice_row<TACC, UW, NT>(vv, M.ci + o, row, wd, gather);
     if (has) epi(row, sum, pv);
   }
+}
+
+// sell_rows with a workgroup step (hook) between the first slice's products and
+// its epilogue, as in sdia_rows_h.
+template <typename TACC, int UW, bool NT, bool REV, typename TM, typename Pre, typename Gather, typename Epi,
+          typename Hook>
+__device__ __forceinline__ bool sell_rows_h(const Mat<TM> &M, int l, int G, Pre pre, Gather gather, Epi epi, Hook hook) {
+  constexpr int NW = kBlock / 64;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int W = G >> 3, x = l & 7, w = l >> 3;
+  const int s0 = (int)((int64_t)x * M.nblk / 8), s1 = (int)((int64_t)(x + 1) * M.nblk / 8);
+  auto slice = [&](int k, auto first) -> bool {
+    const int c = REV ? s1 - 1 - k : s0 + k;
+    const int o0 = ro(M.blk)[c], wd = ro(M.blk)[c + 1] - o0;
+    const int row = c * kSliceRows + lane;
+    const bool has = row < M.n;
+    RowVals<TACC> pv{};
+    if (has) pv = pre(row);
+    const int64_t o = (int64_t)o0 * kSliceRows + lane;
+    GLOBAL const TM *vv = M.val + o;
+    const TACC sum = M.idx16 ? slice_row<TACC, UW, NT>(vv, (GLOBAL const int16_t *)M.ci + o, row, wd, gather)
+                             : slice_row<TACC, UW, NT>(vv, M.ci + o, row, wd, gather);
+    if constexpr (decltype(first)::value)
+      if (!hook()) return false;
+    if (has) epi(row, sum, pv);
+    return true;
+  };
+  int k = w * NW + wv;
+  if (k >= s1 - s0) return hook();
+  if (!slice(k, std::true_type{})) return false;
+  for (k += W * NW; k < s1 - s0; k += W * NW) slice(k, std::false_type{});
+  return true;
 }
 
 // One lane's row of a sliced-diagonal slice: value k of the row multiplies
@@ -665,44 +736,73 @@ __device__ __forceinline__ void bsr_rows(const Mat<TM> &M, int l, int G, Pre pre
 // in any layout, with the matrix's load policy.
 // DIAG: pre(row).a is the gathered operand at column row (the sliced-diagonal
 // walk then reuses it for a diagonal entry).
-template <typename TACC, int UW, bool NT, bool REV, bool DIAG = false, typename TM, typename Pre, typename Gather,
-          typename Epi>
-__device__ __forceinline__ void for_rows_as(const Mat<TM> &M, int l, int G, TACC *lds, Pre pre, Gather gather,
-                                            Epi epi) {
+// UW: loads in flight per lane in sliced rows of more than 4 entries; US:
+// products in flight per thread in CSR (stage_products). hook: a workgroup step before the first
+// epilogue, after the first products where the layout allows it.
+template <typename TACC, int UW, int US, bool NT, bool REV, bool DIAG = false, typename TM, typename Pre,
+          typename Gather, typename Epi, typename Hook>
+__device__ __forceinline__ bool for_rows_as(const Mat<TM> &M, int l, int G, TACC *lds, Pre pre, Gather gather, Epi epi,
+                                            Hook hook) {
   if (M.fmt == FMT_SELL) {
-    sell_rows<TACC, UW, NT, REV>(M, l, G, pre, gather, epi);
+    if constexpr (std::is_same_v<Hook, NoHook>) {
+      sell_rows<TACC, UW, NT, REV>(M, l, G, pre, gather, epi);
+      return true;
+    } else {
+      return sell_rows_h<TACC, UW, NT, REV>(M, l, G, pre, gather, epi, hook);
+    }
   } else if (M.fmt == FMT_SDIA) {
-    sdia_rows<TACC, UW, NT, REV, DIAG>(M, l, G, pre, gather, epi);
+    if constexpr (std::is_same_v<Hook, NoHook>) {
+      sdia_rows<TACC, UW, NT, REV, DIAG>(M, l, G, pre, gather, epi);
+      return true;
+    } else {
+      return sdia_rows_h<TACC, UW, NT, REV>(M, l, G, pre, gather, epi, hook);
+    }
   } else if (M.fmt == FMT_BSR3) {
+    if (!hook()) return false;
     bsr_rows<TACC, NT>(M, l, G, pre, gather, epi);
+    return true;
   } else {
     const Sched sc = sched(M.nblk, l, G);
-    for (int b = sc.first; b < sc.end; b += sc.stride) stream_block<TACC, NT>(M, b, lds, pre, gather, epi);
+    int b = sc.first;
+    if constexpr (!std::is_same_v<Hook, NoHook>) {
+      if (b >= sc.end) return hook();
+      if (!stream_block<TACC, US, NT>(M, b, lds, pre, gather, epi, hook)) return false;
+      b += sc.stride;
+    }
+    for (; b < sc.end; b += sc.stride) stream_block<TACC, US, NT>(M, b, lds, pre, gather, epi, NoHook{});
+    return true;
   }
 }
 
-template <typename TACC, int UW = 4, bool REV = false, bool DIAG = false, typename TM, typename Pre, typename Gather,
-          typename Epi>
+template <typename TACC, int UW = 4, int US = 0, bool REV = false, bool DIAG = false, typename TM,
+          typename Pre, typename Gather, typename Epi>
 __device__ __forceinline__ void for_rows(const Mat<TM> &M, int l, int G, TACC *lds, Pre pre, Gather gather, Epi epi) {
   if (M.temporal)
-    for_rows_as<TACC, UW, false, REV, DIAG>(M, l, G, lds, pre, gather, epi);
+    for_rows_as<TACC, UW, US, false, REV, DIAG>(M, l, G, lds, pre, gather, epi, NoHook{});
   else
-    for_rows_as<TACC, UW, true, REV, DIAG>(M, l, G, lds, pre, gather, epi);
+    for_rows_as<TACC, UW, US, true, REV, DIAG>(M, l, G, lds, pre, gather, epi, NoHook{});
 }
 
-// for_rows with a workgroup step (hook, as in sdia_rows_h) before the first
-// epilogue: over sliced diagonals after the first slice's products, in the
-// other layouts before the walk. Returns hook's result.
-template <typename TACC, int UW = 4, typename TM, typename Pre, typename Gather, typename Epi, typename Hook>
-__device__ __forceinline__ bool for_rows_h(const Mat<TM> &M, int l, int G, TACC *lds, Pre pre, Gather gather,
-                                           Epi epi, Hook hook) {
-  if (M.fmt == FMT_SDIA) {
+// for_rows with a workgroup step (hook) before the first epilogue: after the
+// first slice's products over sliced diagonals, and in the other layouts with
+// EARLY (kernels built for one layout), else before the walk. Returns hook's
+// result.
+template <typename TACC, int UW, int US, bool EARLY, typename TM, typename Pre, typename Gather, typename Epi,
+          typename Hook>
+__device__ __forceinline__ bool for_rows_h(const Mat<TM> &M, int l, int G, TACC *lds, Pre pre, Gather gather, Epi epi,
+                                           Hook hook) {
+  if (!EARLY && M.fmt != FMT_SDIA) {
+    if (!hook()) return false;
+    for_rows<TACC, UW, US>(M, l, G, lds, pre, gather, epi);
+    return true;
+  }
+  if constexpr (EARLY) {
+    if (M.temporal) return for_rows_as<TACC, UW, US, false, false>(M, l, G, lds, pre, gather, epi, hook);
+    return for_rows_as<TACC, UW, US, true, false>(M, l, G, lds, pre, gather, epi, hook);
+  } else {
     if (M.temporal) return sdia_rows_h<TACC, UW, false, false>(M, l, G, pre, gather, epi, hook);
     return sdia_rows_h<TACC, UW, true, false>(M, l, G, pre, gather, epi, hook);
   }
-  if (!hook()) return false;
-  for_rows<TACC, UW>(M, l, G, lds, pre, gather, epi);
-  return true;
 }
 
 // ---- inner products

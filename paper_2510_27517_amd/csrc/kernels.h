@@ -231,6 +231,13 @@ hipError_t launch_iter_GT(const Types &ty, const LaunchSet &L, int mode, hipStre
 hipError_t launch_iter_G(const Types &ty, const LaunchSet &L, bool has_eps, int mode, hipStream_t s,
                          hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr, uint64_t *report = nullptr);
 
+// The same for a single system whose matrix is in sliced ELL, 3x3 blocks or CSR
+// row blocks, by kernels built for that layout alone (single.hip).
+hipError_t launch_one_A(const Types &ty, const LaunchSet &L, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_one_GT(const Types &ty, const LaunchSet &L, int mode, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_one_G(const Types &ty, const LaunchSet &L, bool has_eps, int mode, hipStream_t s, hipEvent_t e0,
+                        hipEvent_t e1, uint64_t *report);
+
 // The three kernels of an ordinary iteration (mode 0) over stencil storage;
 // par: the parity of the iteration index i (it selects the r and d slots).
 // Grids and partial sums are those of the system's record (A.grid, GT.grid,

@@ -23,7 +23,7 @@ __global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_spmv(DevCSR Md, const 
   GLOBAL const TX *__restrict__ x = gl(x_);
   GLOBAL TY *__restrict__ y = gl(y_);
   GLOBAL const double *z = gl(z_);
-  for_rows<TV, 8>(
+  for_rows<TV, 8, 8>(
       M, blockIdx.x, gridDim.x, lds,
       [&](int row) { return RowVals<TV>{AXPY ? (TV)z[row] : (TV)0, (TV)0, (TV)0}; },
       [&](int j) -> TV { return (TV)x[j]; },

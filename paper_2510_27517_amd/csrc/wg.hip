@@ -21,7 +21,7 @@ __device__ __forceinline__ void wg_totals(Acc (&v)[NV], double (&out)[NV], Acc *
 // system's matrices stay in L2 from one iteration to the next.
 template <typename TACC, int UW, bool REV, typename TM, typename Pre, typename Gather, typename Epi>
 __device__ __forceinline__ void wg_rows(const Mat<TM> &M, TACC *lds, Pre pre, Gather gather, Epi epi) {
-  for (int l = 0; l < 8; ++l) for_rows_as<TACC, UW, false, REV>(M, l, 8, lds, pre, gather, epi);
+  for (int l = 0; l < 8; ++l) for_rows_as<TACC, UW, 4, false, REV>(M, l, 8, lds, pre, gather, epi, NoHook{});
   __syncthreads();
 }
 
