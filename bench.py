@@ -53,7 +53,7 @@ HBM_PEAK_GBPS = 8000.0
 N_SIDE = 128
 TOL = 1e-8
 MAXIT = 5000
-KERNEL_SOURCES = ["paper_2510_27517_amd/csrc/" + f for f in ("kernels.hip", "dia.hip", "kernels.h", "device.h")]
+KERNEL_SOURCES = ["paper_2510_27517_amd/csrc/" + f for f in ("kernels.hip", "iter.h", "dia.hip", "kernels.h", "device.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 SECTIONS = ["mixed", "sai_loss", "autotune", "small", "batched", "serving", "elasticity", "synthetic"]
 # long runs, only when named: the serving workload at its configured length
