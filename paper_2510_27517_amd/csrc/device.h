@@ -164,13 +164,14 @@ __device__ __forceinline__ TACC lds_row_sum(const TACC *lds, int a, int e, TACC 
 
 // Products [c0, c1) of a row block into LDS (from c0's slot on). What bounds a
 // block is two dependent memory latencies per round (column, then gather).
-// U > 0: each thread takes U entries a round with all their loads in flight; a
-// round's surplus repeats the last entry (in bounds) and is not stored. U = 0: a
-// plain loop unrolled by four, whose remainder runs one entry after the other.
+// U > 1: each thread takes U entries a round with all their loads in flight; a
+// round's surplus repeats the last entry (in bounds) and is not stored. U = 0, 1:
+// a plain loop unrolled by four, whose remainder runs one entry after the other
+// (1: with the block's bounds from scalar loads, as for U > 1).
 // Which is faster depends on the kernel's types: see the kernels' US.
 template <typename TACC, int U, bool NT, typename TM, typename Gather>
 __device__ __forceinline__ void stage_products(const Mat<TM> &M, int c0, int c1, TACC *lds, Gather gather) {
-  if constexpr (U == 0) {
+  if constexpr (U <= 1) {
 #pragma unroll 4
     for (int k = c0 + (int)threadIdx.x; k < c1; k += kBlock)
       lds[k - c0] = (TACC)ldval<NT>(M.val, k) * gather(ldstream<NT>(M.ci, k));
@@ -204,8 +205,13 @@ __device__ __forceinline__ bool stream_block(const Mat<TM> &M, int b, TACC *lds,
                                              Hook hook) {
   constexpr int cap = kLdsBytes / (int)sizeof(TACC);
   const int tid = threadIdx.x;
-  CONSTANT const int32_t *blk = ro(M.blk) + 2 * b;
-  const int r0 = blk[0], k0 = blk[1], r1 = blk[2], k1 = blk[3];
+  int r0, k0, r1, k1;
+  if constexpr (U == 0) {
+    r0 = M.blk[2 * b], k0 = M.blk[2 * b + 1], r1 = M.blk[2 * b + 2], k1 = M.blk[2 * b + 3];
+  } else {  // scalar loads
+    CONSTANT const int32_t *blk = ro(M.blk) + 2 * b;
+    r0 = blk[0], k0 = blk[1], r1 = blk[2], k1 = blk[3];
+  }
   if (k1 - k0 <= cap) {
     const int row = r0 + tid;
     const bool has = row < r1;

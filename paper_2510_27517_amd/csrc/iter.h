@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_iter_A(const SysDev *_
   // staged products in flight per thread: eight in FP64 (A-kernel of a graph of
   // 600,001: 19.4 -> 15.9 us, of 150,001: 7.7 -> 6.9), but in FP32 the plain
   // loop is faster (15.6 against 16.3 us, 5.5 against 5.9)
-  constexpr int US = FMT >= 0 && sizeof(TV) == 8 ? 8 : 0;
+  constexpr int US = FMT < 0 ? 0 : sizeof(TV) == 8 ? 8 : 1;
   __shared__ TV lds[kLdsBytes / sizeof(TV)];
   __shared__ Acc sh[4 * (kBlock / 64)];
   const Work wk = work_of(dir, map, one);

@@ -572,9 +572,19 @@ static inline int ew_grid(int64_t n) {
   const SysDev one = L.one ? *L.one : SysDev{};        \
   const int2 *map = L.one ? nullptr : (lmap)
 
+// Whether a single system's product takes the kernels built for one layout: not
+// sliced diagonals (the kernels here hold their two-row walk), and not CSR of
+// long rows, where a block holds few rows and the threads that sum them bound
+// it: at 470 entries per row (72,000 rows) the A-kernel takes 237 us here against
+// 255 in FP64 and the G^T-kernel (237 per row) 152 against 167 in FP32; at 145
+// and 76 per row (40,000 rows) an iteration takes 92.5 us against 91.4 there.
+static bool one_layout(const DevCSR &M) {
+  return M.fmt != FMT_SDIA && !(M.fmt == FMT_CSR && (int64_t)M.nnz > (int64_t)192 * M.n);
+}
+
 hipError_t launch_iter_A(const Types &ty, const LaunchSet &L, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (L.nA == 0) return hipSuccess;
-  if (L.one && L.one->A.fmt != FMT_SDIA) return launch_one_A(ty, L, s, e0, e1);
+  if (L.one && one_layout(L.one->A)) return launch_one_A(ty, L, s, e0, e1);
   const bool u4 = L.uw_a == 4;
   PCG_ONE(L.mapA);
   if (ty.vec == F64 && ty.a == F64) {
@@ -596,7 +606,7 @@ hipError_t launch_iter_A(const Types &ty, const LaunchSet &L, hipStream_t s, hip
 hipError_t launch_iter_GT(const Types &ty, const LaunchSet &L, int mode, hipStream_t s, hipEvent_t e0,
                           hipEvent_t e1) {
   if (L.nGT == 0) return hipSuccess;
-  if (L.one && L.one->GT.fmt != FMT_SDIA) return launch_one_GT(ty, L, mode, s, e0, e1);
+  if (L.one && one_layout(L.one->GT)) return launch_one_GT(ty, L, mode, s, e0, e1);
   PCG_ONE(L.mapGT);
   PCG_DISPATCH_V(ty.vec, TV, PCG_DISPATCH_G(ty.g, TG, {
     PCG_LAUNCH((k_iter_GT<TV, TG>), L.nGT, s, e0, e1, L.dir, map, one, mode);
@@ -607,7 +617,7 @@ hipError_t launch_iter_GT(const Types &ty, const LaunchSet &L, int mode, hipStre
 hipError_t launch_iter_G(const Types &ty, const LaunchSet &L, bool has_eps, int mode, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1, uint64_t *report) {
   if (L.nG == 0) return hipSuccess;
-  if (L.one && L.one->G.fmt != FMT_SDIA) return launch_one_G(ty, L, has_eps, mode, s, e0, e1, report);
+  if (L.one && one_layout(L.one->G)) return launch_one_G(ty, L, has_eps, mode, s, e0, e1, report);
   PCG_ONE(L.mapG);
   PCG_DISPATCH_V(ty.vec, TV, PCG_DISPATCH_G(ty.g, TG, {
     if (has_eps)
