@@ -316,8 +316,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, (NW 
       delta = dn;
       apply_g(beta);
     }
-    if (status == ST_BREAK_GAMMA || status == ST_BREAK_DELTA) break;
-    // the true residual b - A x
+    // the true residual b - A x, after a breakdown too
     residual(x);
     {
       Acc a{0.0, 0.0};
