@@ -211,8 +211,7 @@ __device__ __forceinline__ void solve_wg(const SysDev &D, GLOBAL State *st, cons
           });
       it = i1;
     }
-    if (status == ST_BREAK_GAMMA || status == ST_BREAK_DELTA) break;
-    // the true residual b - A x into the current r slot
+    // the true residual b - A x into the current r slot, after a breakdown too
     residual(rv[it & 1], true);
     if (status == ST_CONV_REC && S0.confirm && !(sqrt(true_rr) <= tol_nb)) {
       ++o.restarts;  // the recurrence drifted: restart from the true residual
