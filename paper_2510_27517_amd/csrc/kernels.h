@@ -274,12 +274,13 @@ hipError_t launch_solve_wg(const Types &ty, const LaunchSet &L, bool has_eps, hi
 // distinct column offsets in all, listed ascending; n <= wgs_max_n; pad at
 // least the largest |offset|; wgs_lds_bytes of dynamic LDS. b and x (x0 in,
 // solution out) are FP64 when io64, else of the vector type. The final
-// state goes to st[0] and to host (page-locked host memory).
+// state goes to st[0] and to host (page-locked host memory). keep (or null): b
+// in the vector type, for later work on the system's last right-hand side.
 constexpr int kWgsMaxN = 2048, kWgsMaxA = 7, kWgsMaxG = 4;
 struct WgsArgs {
   DevCSR A, GT, G;
   const void *b = nullptr;
-  void *x = nullptr;
+  void *x = nullptr, *keep = nullptr;
   State *st = nullptr, *host = nullptr;
   int32_t n = 0, pad = 0, io64 = 0, na = 0, nt = 0, ng = 0;
   int32_t offA[kWgsMaxA] = {}, offT[kWgsMaxG] = {}, offG[kWgsMaxG] = {};

@@ -1360,6 +1360,7 @@ int solve_core(pcg_ctx *ctx, const Core &c, double tol, int maxit, CoreOut &out,
     P.b = io ? (const void *)io->b : D.b;
     P.x = io ? (void *)io->x : D.x;
     P.io64 = io != nullptr;
+    P.keep = io ? D.b : nullptr;  // pcg_time_kernels solves the last right-hand side again
     P.st = D.st;
     P.host = ctx->h_states + 2 * c.slot;
     P.n = D.n;

@@ -182,6 +182,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, (NW 
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
       const TV b = rhs(j);
+      if (P.keep && has(j)) gl((TV *)P.keep)[tid + j * NT] = b;
       acc_prod(a, b, b);
     }
     bb = total1<NW>(a, sh);
