@@ -852,16 +852,20 @@ __device__ __forceinline__ void acc_prod(Acc &x, float a, float b) {
   x.lo = x.lo + e;
 }
 
-// a + b. The low words add plainly, without a renormalisation of the pair
-// (as each lane's own accumulation does: the bound above is Dot2's either
-// way): 8 FP64 operations, 6 of them dependent, instead of 14 and 12. The
-// reductions of one iteration are about a hundred of these one after the
-// other, two nanoseconds per operation.
+// a + b, normalised (hi = fl(hi + lo)): 11 FP64 operations, 9 of them
+// dependent. The pair is renormalised by Dekker's Fast2Sum, which gives what
+// TwoSum would (three operations more): s is zero, far above t, or a multiple
+// of t's last place. Without the renormalisation (8 operations, 6 dependent) the
+// low words grow through a tree of sums and their roundings with them: over
+// 131,072 lanes the pair's error was twice as large (squares 7.0e-33 of the
+// terms' magnitude against 3.6e-33).
 __device__ __forceinline__ Acc acc_add(Acc a, Acc b) {
+  double s, e;
+  two_sum(a.hi, b.hi, s, e);
+  const double t = (a.lo + b.lo) + e;
   Acc r;
-  double e;
-  two_sum(a.hi, b.hi, r.hi, e);
-  r.lo = (a.lo + b.lo) + e;
+  r.hi = s + t;
+  r.lo = t - (r.hi - s);
   return r;
 }
 
@@ -914,6 +918,17 @@ __device__ __forceinline__ Acc wave_total2(Acc a, Acc b) {
   v = acc_add(v, acc_dpp<0x141>(v));
   v = acc_add(v, acc_dpp<0x140>(v));
   v = acc_add(v, acc_dpp<0x142>(v));
+  return v;
+}
+
+// The total of each group of N adjacent lanes (a power of two up to 8), in all of
+// the group.
+template <int N>
+__device__ __forceinline__ Acc lanes_total(Acc v) {
+  static_assert(N == 1 || N == 2 || N == 4 || N == 8, "lanes");
+  if constexpr (N >= 2) v = acc_add(v, acc_dpp<0xB1>(v));
+  if constexpr (N >= 4) v = acc_add(v, acc_dpp<0x4E>(v));
+  if constexpr (N >= 8) v = acc_add(v, acc_dpp<0x141>(v));
   return v;
 }
 
@@ -998,9 +1013,11 @@ __device__ __forceinline__ double uniform(double v) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// The wave totals meet in LDS after one barrier, and every thread adds them
-// in the same order. They sit in sh[2 NW, 2 NW + NV NW), apart from
-// block_sum's slots, so that a block_sum later in the kernel cannot
+// The wave totals meet in LDS after one barrier, and each wave adds them
+// across its lanes: two additions in sequence for both values at once (with
+// every lane adding all of them, a solve of 2025 rows by the one-workgroup
+// stencil solver takes 385 us against 354). They sit in sh[2 NW, 2 NW + NV NW),
+// apart from block_sum's slots, so that a block_sum later in the kernel cannot
 // overwrite them while a slower wave still reads them; callers put a barrier
 // between two calls.
 template <int NV>
@@ -1010,11 +1027,10 @@ __device__ __forceinline__ void reduce_partials(Acc (&acc)[NV], double (&out)[NV
   Acc *shr = sh + 2 * NW;
   put_wave_totals<NV>(acc, shr);
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const Acc a = add_waves(shr + j * NW);
-    out[j] = uniform(a.hi + a.lo);
-  }
+  const int lane = threadIdx.x & 63;
+  const Acc a = lanes_total<NW>(shr[(NV == 2 ? (lane >> 5) * NW : 0) + (lane & (NW - 1))]);
+  out[0] = readlane_f64(a.hi + a.lo, 0);
+  if constexpr (NV == 2) out[1] = readlane_f64(a.hi + a.lo, 32);
 }
 
 template <int NV>

@@ -46,14 +46,9 @@ __device__ __forceinline__ double total1(Acc a, LDSP Acc *sh) {
       sh[w].lo = a.lo;
     }
     __syncthreads();
-    Acc v[NW];
-#pragma unroll
-    for (int q = 0; q < NW; ++q) v[q] = Acc{sh[q].hi, sh[q].lo};
-#pragma unroll
-    for (int h = NW / 2; h >= 1; h /= 2)
-#pragma unroll
-      for (int q = 0; q < h; ++q) v[q] = acc_add(v[q], v[q + h]);
-    return uniform(v[0].hi + v[0].lo);
+    const int q = lane & (NW - 1);
+    const Acc v = lanes_total<NW>(Acc{sh[q].hi, sh[q].lo});
+    return uniform(v.hi + v.lo);
   }
 }
 template <int NW>
@@ -70,16 +65,10 @@ __device__ __forceinline__ void total2(Acc a, Acc b, double &ta, double &tb, LDS
     }
     __syncthreads();
     // lanes of the lower half add the first value's waves, the upper the second's
-    const int o = (lane >> 5) * NW;
-    Acc v[NW];
-#pragma unroll
-    for (int q = 0; q < NW; ++q) v[q] = Acc{sh[o + q].hi, sh[o + q].lo};
-#pragma unroll
-    for (int h = NW / 2; h >= 1; h /= 2)
-#pragma unroll
-      for (int q = 0; q < h; ++q) v[q] = acc_add(v[q], v[q + h]);
-    ta = readlane_f64(v[0].hi + v[0].lo, 0);
-    tb = readlane_f64(v[0].hi + v[0].lo, 32);
+    const int q = (lane >> 5) * NW + (lane & (NW - 1));
+    const Acc v = lanes_total<NW>(Acc{sh[q].hi, sh[q].lo});
+    ta = readlane_f64(v.hi + v.lo, 0);
+    tb = readlane_f64(v.hi + v.lo, 32);
   }
 }
 
