@@ -461,12 +461,26 @@ void sell_bytes(int32_t n, const int32_t *rp, const uint8_t *in, size_t esz, con
   }
 }
 
-// The distinct offsets of slice c's entries, ascending.
+// The distinct offsets of slice c's entries, ascending. Rows and d are
+// ascending, so each row merges into d, which after a stencil's first row already
+// holds (nearly) all of the slice's offsets. Where rows share few offsets d
+// outgrows them, and inserting would take time quadratic in the slice's offsets:
+// from there on the rest of the slice is gathered, sorted and made unique (22
+// slices of 470 random columns per row, one thread: 38 ms, as by sorting alone,
+// by merging alone 188; 60,000 rows of 7 diagonals 0.6 ms, by sorting 3.0).
 static void slice_offsets(int32_t n, const int32_t *rp, const int32_t *ci, int32_t c, std::vector<int32_t> &d) {
-  // rows and d are ascending: each row merges into d, which after a stencil's
-  // first row already holds (nearly) all of the slice's offsets
   d.clear();
-  for (int32_t r = c * kSlice; r < std::min(n, (c + 1) * kSlice); ++r) {
+  const int32_t r1 = std::min(n, (c + 1) * kSlice);
+  size_t longest = 0;
+  for (int32_t r = c * kSlice; r < r1; ++r) {
+    longest = std::max(longest, (size_t)(rp[r + 1] - rp[r]));
+    if (d.size() > 2 * longest + kSlice) {
+      for (; r < r1; ++r)
+        for (int32_t q = rp[r]; q < rp[r + 1]; ++q) d.push_back(ci[q] - r);
+      std::sort(d.begin(), d.end());
+      d.erase(std::unique(d.begin(), d.end()), d.end());
+      return;
+    }
     size_t k = 0;
     for (int32_t q = rp[r]; q < rp[r + 1]; ++q, ++k) {
       const int32_t o = ci[q] - r;

@@ -1,0 +1,127 @@
+"""The pattern scan of the sliced-diagonal layout (host code, compiled here):
+the right offsets for every kind of slice, and no slower than sorting each
+slice's offsets where rows share none, nor on stencils."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2510_27517_amd", "csrc")
+
+HARNESS = """
+#include <chrono>
+#include "host.h"
+using namespace pcgh;
+static void by_sorting(int32_t n, const int32_t *rp, const int32_t *ci, std::vector<int32_t> &so,
+                       std::vector<int32_t> &offs) {
+  so.assign(1, 0);
+  offs.clear();
+  std::vector<int32_t> d;
+  for (int32_t c = 0; c * kSlice < n; ++c) {
+    d.clear();
+    for (int32_t r = c * kSlice; r < std::min(n, (c + 1) * kSlice); ++r)
+      for (int32_t q = rp[r]; q < rp[r + 1]; ++q) d.push_back(ci[q] - r);
+    std::sort(d.begin(), d.end());
+    d.erase(std::unique(d.begin(), d.end()), d.end());
+    offs.insert(offs.end(), d.begin(), d.end());
+    so.push_back((int32_t)offs.size());
+  }
+}
+extern "C" int same(int32_t n, const int32_t *rp, const int32_t *ci, int threads) {
+  std::vector<int32_t> so, offs, so2, offs2;
+  by_sorting(n, rp, ci, so, offs);
+  return sdia_pattern(n, rp, ci, INT64_MAX, so2, offs2, threads) && so == so2 && offs == offs2 &&
+         sdia_entries(n, rp, ci) == (int64_t)offs.size() * kSlice;
+}
+extern "C" void times(int32_t n, const int32_t *rp, const int32_t *ci, double *ms) {  // library, sorting
+  ms[0] = ms[1] = 1e30;
+  for (int rep = 0; rep < 7; ++rep)
+    for (int w = 0; w < 2; ++w) {
+      std::vector<int32_t> so, offs;
+      const auto t0 = std::chrono::steady_clock::now();
+      if (w)
+        by_sorting(n, rp, ci, so, offs);
+      else
+        sdia_pattern(n, rp, ci, INT64_MAX, so, offs, 1);
+      ms[w] = std::min(ms[w], std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count());
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    from paper_2510_27517_amd import build
+
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("hipcc not installed")
+    d = tmp_path_factory.mktemp("offsets")
+    (d / "h.cpp").write_text(HARNESS)
+    inc = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build.HIPCC))), "include")
+    subprocess.run([build.HIPCC, *build.COMMON, "-x", "c++", "-D__HIP_PLATFORM_AMD__", f"-I{inc}", "-shared",
+                    str(d / "h.cpp"), os.path.join(CSRC, "host.cpp"), "-o", str(d / "h.so"), "-lpthread"], check=True)
+    return ctypes.CDLL(str(d / "h.so"))
+
+
+def _random(n, per_row, seed):
+    rng = np.random.default_rng(seed)
+    rows = [np.unique(rng.integers(0, n, per_row)) for _ in range(n)]
+    rp = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int32)
+    return rp, np.concatenate(rows).astype(np.int32)
+
+
+def _head(n, rows, per_row, seed):
+    """Random rows first (the scan turns such a pattern down after a few
+    slices), then rows of a diagonal."""
+    rng = np.random.default_rng(seed)
+    head = [np.unique(rng.integers(0, n, per_row)) for _ in range(rows)]
+    sizes = [r.size for r in head] + [1] * (n - rows)
+    return (np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32),
+            np.concatenate(head + [np.arange(rows, n)]).astype(np.int32))
+
+
+def _band(n, offsets):
+    rows = [[i + o for o in offsets if 0 <= i + o < n] for i in range(n)]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    return rp, np.concatenate(rows).astype(np.int32)
+
+
+def _joined(a, b):
+    """Slices of both kinds, and rows of both kinds within one slice."""
+    return np.concatenate([a[0], a[0][-1] + b[0][1:]]).astype(np.int32), np.concatenate([a[1], b[1]])
+
+
+PATTERNS = {
+    "stencil": lambda: _band(4000, [-700, -20, -1, 0, 1, 20, 700]),
+    "wide_band": lambda: _band(1500, list(range(-150, 151))),
+    "random_short": lambda: _random(3000, 5, 1),
+    "random_long": lambda: _random(3000, 300, 2),
+    "tail": lambda: _random(65, 40, 3),
+    "one_row": lambda: _random(1, 1, 4),
+    "stencil_then_random": lambda: _joined(_band(1000, [-30, -1, 0, 1, 30]), _random(1000, 100, 5)),
+    "random_then_stencil": lambda: _joined(_random(1000, 100, 6), _band(1000, [-30, -1, 0, 1, 30])),
+}
+
+
+@pytest.mark.parametrize("name", sorted(PATTERNS))
+def test_offsets(lib, name):
+    rp, ci = PATTERNS[name]()
+    for threads in (1, 4):
+        assert lib.same(rp.size - 1, rp.ctypes.data_as(ctypes.c_void_p), ci.ctypes.data_as(ctypes.c_void_p), threads)
+
+
+# inserting every new offset into the sorted ones took five times as long as
+# sorting on the first pattern; sorting takes five times as long on the last
+@pytest.mark.parametrize("pattern", [lambda: _head(72000, 1408, 470, 7), lambda: _head(40000, 640, 1000, 8),
+                                     lambda: _head(20000, 20000, 21, 9),
+                                     lambda: _band(60000, [-2500, -50, -1, 0, 1, 50, 2500])],
+                         ids=["470_per_row", "1000_per_row", "21_per_row", "stencil"])
+def test_time(lib, pattern):
+    rp, ci = pattern()
+    ms = np.zeros(2)
+    lib.times(rp.size - 1, rp.ctypes.data_as(ctypes.c_void_p), ci.ctypes.data_as(ctypes.c_void_p),
+              ms.ctypes.data_as(ctypes.c_void_p))
+    assert ms[0] <= 2.0 * ms[1], ms
