@@ -530,13 +530,35 @@ bool sdia_pattern(int32_t n, const int32_t *rp, const int32_t *ci, int64_t cap, 
   return true;
 }
 
-void store_value(int dt, double x, uint8_t *p) {
+namespace {
+// A storage type's conversion of x into the bytes at p (inlined, the type
+// known, into the loops over a matrix's values).
+template <int DT>
+inline void store_value(double x, uint8_t *p) {
   const auto put = [&](auto u) { std::memcpy(p, &u, sizeof u); };
+  if constexpr (DT == pcgk::F64)
+    put(x);
+  else if constexpr (DT == pcgk::F32)
+    put((float)x);
+  else if constexpr (DT == pcgk::BF16)
+    put(to_bf16_bits(x));
+  else
+    put(to_f16_bits(x));
+}
+
+template <int DT>
+void cast_all(const double *v, int64_t nnz, double scale, uint8_t *out) {
+  for (int64_t k = 0; k < nnz; ++k) store_value<DT>(v[k] * scale, out + (size_t)k * pcgk::dtype_size(DT));
+}
+}  // namespace
+
+void cast_values(const double *v, int64_t nnz, int dt, double scale, Bytes &out) {
+  out.resize(pcgk::dtype_size(dt) * (size_t)std::max<int64_t>(nnz, 1));
   switch (dt) {
-    case pcgk::F64: put(x); break;
-    case pcgk::F32: put((float)x); break;
-    case pcgk::BF16: put(to_bf16_bits(x)); break;
-    default: put(to_f16_bits(x)); break;
+    case pcgk::F64: cast_all<pcgk::F64>(v, nnz, scale, out.data()); break;
+    case pcgk::F32: cast_all<pcgk::F32>(v, nnz, scale, out.data()); break;
+    case pcgk::BF16: cast_all<pcgk::BF16>(v, nnz, scale, out.data()); break;
+    default: cast_all<pcgk::F16>(v, nnz, scale, out.data()); break;
   }
 }
 
@@ -553,7 +575,7 @@ void place_slices(int32_t n, const int32_t *rp, const int32_t *ci, const double 
     int32_t k = so[c];
     for (int32_t q = rp[r]; q < rp[r + 1]; ++q) {  // both ascending: one merge pass
       while (offs[k] != ci[q] - r) ++k;
-      store_value(DT, v[q] * scale, out + ((size_t)k * kSlice + l) * esz);
+      store_value<DT>(v[q] * scale, out + ((size_t)k * kSlice + l) * esz);
     }
   }
 }

@@ -136,9 +136,8 @@ int64_t sdia_entries(int32_t n, const int32_t *rp, const int32_t *ci, int64_t st
 bool sdia_pattern(int32_t n, const int32_t *rp, const int32_t *ci, int64_t cap, std::vector<int32_t> &so,
                   std::vector<int32_t> &offs, int threads);
 
-// A storage type's conversion of v * scale (dt a pcgk::Dtype) into the bytes
-// at p.
-void store_value(int dt, double v, uint8_t *p);
+// The values v times scale in dt (a pcgk::Dtype), in their order.
+void cast_values(const double *v, int64_t nnz, int dt, double scale, Bytes &out);
 
 // The values v (CSR order) times scale in dt, in the SDIA order (zeros where a
 // row has no entry).

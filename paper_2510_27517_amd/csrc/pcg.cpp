@@ -329,12 +329,6 @@ int norm_grid(int32_t n) {
   return (int)((g + 7) & ~int64_t(7));
 }
 
-void cast_values(const double *v, int64_t nnz, int dt, double scale, pcgh::Bytes &out) {
-  const size_t esz = pcgk::dtype_size(dt);
-  out.resize(esz * (size_t)std::max<int64_t>(nnz, 1));
-  for (int64_t k = 0; k < nnz; ++k) pcgh::store_value(dt, v[k] * scale, out.data() + (size_t)k * esz);
-}
-
 // Layout choice (pcg_config.layout): the sliced layout when its padding stays
 // small, the CSR row blocks otherwise.
 bool use_sell(int layout, int32_t n, const int32_t *rp) {
@@ -512,7 +506,7 @@ void make_mat(const pcg_config &cfg, int cus, int32_t n, const int32_t *rp, cons
     return;
   }
   pcgh::Bytes csr_val;
-  cast_values(v, M.nnz, dt, scale, csr_val);
+  pcgh::cast_values(v, M.nnz, dt, scale, csr_val);
   if (M.fmt == pcgk::FMT_BSR3)
     pcgh::bsell_bytes(n, rp, csr_val.data(), pcgk::dtype_size(dt), M.blk, M.val);
   else if (M.fmt == pcgk::FMT_SELL)
