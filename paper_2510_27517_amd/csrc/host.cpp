@@ -506,9 +506,11 @@ bool sdia_pattern(int32_t n, const int32_t *rp, const int32_t *ci, int64_t cap, 
   const int32_t ns = (n + kSlice - 1) / kSlice;
   const int64_t grain = kRowGrain / kSlice;
   so.assign(ns + 1, 0);
-  std::vector<std::vector<int32_t>> part(part_count(threads, ns, grain));
+  // counted once: the process's CPUs may change between two counts
+  const int np = part_count(threads, ns, grain);
+  std::vector<std::vector<int32_t>> part(np);
   std::atomic<int64_t> stored{0};
-  parallel_parts(threads, ns, grain, [&](int64_t lo, int64_t hi, int t) {
+  parallel_parts(np, ns, grain, [&](int64_t lo, int64_t hi, int t) {
     std::vector<int32_t> d;
     std::vector<int32_t> &mine = part[t];
     for (int64_t c = lo; c < hi; ++c) {

@@ -19,8 +19,9 @@ unsigned available_cpus();
 // f(lo, hi, part) over [0, n) split into equal parts on up to `threads` threads
 // (0: available_cpus(), at most 16), at least `grain` items each, so small work
 // stays on the calling thread; parts are numbered in ascending order of their
-// ranges, and part_count gives their number beforehand. A part whose thread cannot be started runs on
-// the calling thread; the first exception of any part is thrown here.
+// ranges. Their number beforehand is part_count's, if that is then passed as
+// `threads`. A part whose thread cannot be started runs on the calling thread; the
+// first exception of any part is thrown here.
 inline int part_count(int threads, int64_t n, int64_t grain) {
   const int64_t most = threads > 0 ? threads : (int64_t)std::min(16u, available_cpus());
   return (int)std::max<int64_t>(1, std::min(most, n / std::max<int64_t>(grain, 1)));
