@@ -171,18 +171,21 @@ __device__ __forceinline__ TACC lds_row_sum(const TACC *lds, int a, int e, TACC 
 // Which is faster depends on the kernel's types: see the kernels' US.
 template <typename TACC, int U, bool NT, typename TM, typename Gather>
 __device__ __forceinline__ void stage_products(const Mat<TM> &M, int c0, int c1, TACC *lds, Gather gather) {
+  // unsigned: nonzeros number up to 2^31 - 1, and a round's step past the last
+  // of them must not wrap below zero
+  const uint32_t end = (uint32_t)c1;
   if constexpr (U <= 1) {
 #pragma unroll 4
-    for (int k = c0 + (int)threadIdx.x; k < c1; k += kBlock)
+    for (uint32_t k = (uint32_t)c0 + threadIdx.x; k < end; k += kBlock)
       lds[k - c0] = (TACC)ldval<NT>(M.val, k) * gather(ldstream<NT>(M.ci, k));
   } else {
-    for (int c = c0 + (int)threadIdx.x; c < c1; c += U * kBlock) {
+    for (uint32_t c = (uint32_t)c0 + threadIdx.x; c < end; c += U * kBlock) {
       int32_t col[U];
       TACC v[U];
       decltype(gather(0)) x[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int k = min(c + u * kBlock, c1 - 1);
+        const uint32_t k = min(c + u * kBlock, end - 1);
         col[u] = ldstream<NT>(M.ci, k);
         v[u] = (TACC)ldval<NT>(M.val, k);
       }
@@ -190,7 +193,7 @@ __device__ __forceinline__ void stage_products(const Mat<TM> &M, int c0, int c1,
       for (int u = 0; u < U; ++u) x[u] = gather(col[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (c + u * kBlock < c1) lds[c + u * kBlock - c0] = v[u] * x[u];
+        if (c + u * kBlock < end) lds[c + u * kBlock - c0] = v[u] * x[u];
     }
   }
 }
