@@ -869,6 +869,37 @@ void drop_graphs(pcg_ctx *ctx) {
   ctx->graphs_x.clear();
 }
 
+int upload_dir_entry(pcg_ctx *ctx, int slot) {
+  HIPCHK(hipMemcpy(ctx->d_dir + slot, &ctx->dir[slot], sizeof(SysDev), hipMemcpyHostToDevice));
+  return PCG_OK;
+}
+
+// Frees the single system's stencil storage, a second copy of its values: from
+// here on the general kernels run, with the same results.
+void give_back_stencil(pcg_ctx *ctx) {
+  Sys &S = ctx->single;
+  if (!S.blkD) return;
+  (void)hipStreamSynchronize(ctx->stream);
+  drop_graphs(ctx);
+  ctx->da.put(S.blkD);
+  S.blkD = nullptr;
+  S.diaA = S.diaG = pcgk::DiaOp{};
+  ctx->set_main.L.diaA = ctx->set_main.L.diaG = pcgk::DiaOp{};
+  S.dev.d1 = S.d1;
+  ctx->dir[kSlotMain] = S.dev;
+  (void)upload_dir_entry(ctx, kSlotMain);
+}
+
+// Device memory that the context cannot do without. Where it does not fit,
+// the stencil storage makes room.
+hipError_t device_alloc(pcg_ctx *ctx, void **p, size_t bytes) {
+  const hipError_t e = ctx->da.get(p, bytes);
+  if (e == hipSuccess || !ctx->single.blkD) return e;
+  (void)hipGetLastError();
+  give_back_stencil(ctx);
+  return ctx->da.get(p, bytes);
+}
+
 void free_set(pcg_ctx *ctx, HostSet &hs) {
   if (hs.dev) ctx->da.put(hs.dev);
   hs = HostSet{};
@@ -910,7 +941,7 @@ int build_set(pcg_ctx *ctx, HostSet &hs, const std::vector<int> &slots) {
     hs.cap = kcap;
   } else {
     ctx->da.put(keep);
-    HIPCHK(ctx->da.get(&hs.dev, bytes));
+    HIPCHK(device_alloc(ctx, &hs.dev, bytes));
     hs.cap = bytes;
   }
   if (used) HIPCHK(hipMemcpy(hs.dev, h.data(), used, hipMemcpyHostToDevice));
@@ -944,11 +975,6 @@ int build_set(pcg_ctx *ctx, HostSet &hs, const std::vector<int> &slots) {
 // Kernel knobs of the configuration (0: the defaults).
 int cfg_rows_per_lane(const pcg_config &c) { return c.rows_per_lane == 1 ? 1 : 2; }
 int cfg_loads_in_flight(const pcg_config &c) { return c.loads_in_flight == 4 ? 4 : 8; }
-
-int upload_dir_entry(pcg_ctx *ctx, int slot) {
-  HIPCHK(hipMemcpy(ctx->d_dir + slot, &ctx->dir[slot], sizeof(SysDev), hipMemcpyHostToDevice));
-  return PCG_OK;
-}
 
 void free_sys(pcg_ctx *ctx, Sys &S) {
   if (S.pooled) {
@@ -1542,7 +1568,7 @@ int prepare_escalation(pcg_ctx *ctx) {
   const size_t bytes = 8 * vb + align_up(W * (size_t)ga) * 2 + align_up(2 * W * (size_t)gt) + align_up(W * (size_t)gb) +
                        align_up(4 * bg.size()) + align_up(4 * bgt.size());
   void *blk = nullptr;
-  if (ctx->da.get(&blk, bytes) != hipSuccess) {
+  if (device_alloc(ctx, &blk, bytes) != hipSuccess) {
     (void)hipGetLastError();
     ctx->err = "refinement: allocation for the FP64 inner solve failed";
     return PCG_ENOMEM;
@@ -1851,6 +1877,10 @@ int ensure_pool(pcg_ctx *ctx) {
     cap = fr / 2;
   }
   int rc = ctx->pool.init(cap);
+  if (rc && ctx->single.blkD) {
+    give_back_stencil(ctx);
+    rc = ctx->pool.init(cap);
+  }
   if (rc) ctx->err = "device pool allocation failed";
   return rc;
 }
@@ -2017,7 +2047,7 @@ int place_admitted(pcg_ctx *ctx, std::vector<std::shared_ptr<Req>> &cand, std::v
                         align_up(8 * (size_t)std::max<int64_t>(nnz, 1)) + align_up(4 * (size_t)n) +
                         align_up(4 * (size_t)(n + 1)) + align_up(8 * (size_t)std::max<int64_t>(nl, 1)) + align_up(8);
       void *tmp = nullptr;
-      hipError_t e = ctx->da.get(&tmp, tb);
+      hipError_t e = device_alloc(ctx, &tmp, tb);
       if (e != hipSuccess) return fail_temps(e);
       temps.push_back(tmp);
       Carver c{(uint8_t *)tmp};
@@ -2820,6 +2850,7 @@ int pcg_set_matrix(pcg_ctx *ctx, int32_t n, int64_t nnz, const int32_t *rowptr, 
 static int set_g_from_host(pcg_ctx *ctx, std::vector<int32_t> &grp, std::vector<int32_t> &gci,
                            std::vector<double> &gv) {
   drop_graphs(ctx);
+  give_back_stencil(ctx);  // it holds the old G's values
   if (ctx->single.blkG) {
     ctx->da.put(ctx->single.blkG);
     ctx->single.blkG = nullptr;
@@ -2932,6 +2963,7 @@ static int build_fsai_device(pcg_ctx *ctx) {
     }
   });
   drop_graphs(ctx);
+  give_back_stencil(ctx);  // it holds the old G's values
   if (S.blkG) {
     ctx->da.put(S.blkG);
     S.blkG = nullptr;
@@ -3497,7 +3529,7 @@ int pcg_sai_loss(pcg_ctx *ctx, int32_t k, const double *W, int on_device, double
     ctx->da.put(ctx->loss_buf);
     ctx->loss_buf = nullptr;
     ctx->loss_bytes = 0;
-    if (ctx->da.get(&ctx->loss_buf, need) != hipSuccess) {
+    if (device_alloc(ctx, &ctx->loss_buf, need) != hipSuccess) {
       (void)hipGetLastError();
       ctx->loss_buf = nullptr;
       ctx->err = "pcg_sai_loss: device allocation failed";
