@@ -436,11 +436,12 @@ int pcg_build_g_host(int kind, uint64_t seed, int32_t n, const int32_t *rowptr, 
  * 3x3-block cover), at the configured grid, then for the best layouts at
  * half and twice the grid, then the load policy (each subset of A, G, G^T
  * read with ordinary loads and kept in the memory-side cache, besides the
- * residency plan's choice), then two kernel knobs: rows per lane of the
+ * plan's choice; G and G^T together over stencil storage, which holds one
+ * copy), then two kernel knobs: rows per lane of the
  * G^T- and G-kernels over sliced diagonals (two rows make every access
  * twice as wide, or one) and loads in flight per lane in the A-kernel's sliced rows
- * (8 or 4), and keeps the fastest (a candidate must beat the current best
- * by 3%).
+ * (8 or 4; stencil storage has neither knob), and keeps the fastest (a
+ * candidate must beat the current best by 3%).
  * The matrices are laid out again with the same values, so products stay
  * bit-identical, and inner products are exact: every candidate gives the
  * same solve bit for bit. A layout forced in the configuration is kept; only

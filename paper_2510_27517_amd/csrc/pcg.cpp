@@ -3176,6 +3176,15 @@ static int relayout(pcg_ctx *ctx) {
   return set_g_from_host(ctx, grp, gci, gv);
 }
 
+// Which of A, G and G^T (bits 0, 1, 2) the single system's iteration reads with
+// ordinary loads, from whichever storage it uses.
+static int load_policy(const pcg_ctx *ctx) {
+  const Sys &S = ctx->single;
+  const int a = S.diaA.nd ? S.diaA.temporal : S.dev.A.temporal;
+  if (S.diaG.nd) return a | (S.diaG.temporal ? 6 : 0);
+  return a | (S.dev.G.temporal << 1) | (S.dev.GT.temporal << 2);
+}
+
 // One CG iteration's time (three kernels) on the stored right-hand side b = 1:
 // the smaller of two timings of `iters` iterations after as many for warm-up.
 static int time_iteration(pcg_ctx *ctx, int iters, double *ms) {
@@ -3303,7 +3312,7 @@ int pcg_autotune(pcg_ctx *ctx, int iters, pcg_tune_result *res) {
       if ((rc = consider(t))) return rc;
     }
     // load policy for the best layouts and grid: every subset of {A, G, G^T}
-    // read with ordinary loads (the residency plan's choice was timed above)
+    // read with ordinary loads, but for the plan's own choice, timed above
     base = best;
     if (!base.on) {
       base.on = true;
@@ -3311,16 +3320,20 @@ int pcg_autotune(pcg_ctx *ctx, int iters, pcg_tune_result *res) {
       base.lg = ctx->cfg.layout;
       base.gm = gm0;
     }
-    const int planned = residency_plan(ctx);
+    // (the context is laid out as base); over stencil storage G^T's values serve
+    // both products, so only half of the subsets differ
+    unsigned timed = 1u << load_policy(ctx);
     for (int r = 0; r < 8; ++r) {
-      if (r == planned) continue;
+      const int used = ctx->single.diaG.nd && (r & 6) ? r | 6 : r;
+      if (timed >> used & 1) continue;
+      timed |= 1u << used;
       pcg_ctx::Tune t = base;
       t.res = r;
       if ((rc = consider(t))) return rc;
     }
     // kernel knobs for the best of the above: rows per lane of the G^T-kernel
     // (vector width of its accesses over sliced diagonals), then loads in
-    // flight per lane in the A-kernel
+    // flight per lane in the A-kernel (the stencil kernels have neither)
     base = best;
     if (!base.on) {
       base.on = true;
@@ -3328,13 +3341,13 @@ int pcg_autotune(pcg_ctx *ctx, int iters, pcg_tune_result *res) {
       base.lg = ctx->cfg.layout;
       base.gm = gm0;
     }
-    {
+    if (!ctx->single.diaG.nd) {
       pcg_ctx::Tune t = base;
       t.gt_rows = base.gt_rows == 2 ? 1 : 2;
       if ((rc = consider(t))) return rc;
     }
     base = best.on ? best : base;
-    {
+    if (!ctx->single.diaA.nd) {
       pcg_ctx::Tune t = base;
       t.a_uw = base.a_uw == 8 ? 4 : 8;
       if ((rc = consider(t))) return rc;
@@ -3355,8 +3368,7 @@ int pcg_autotune(pcg_ctx *ctx, int iters, pcg_tune_result *res) {
     res->fmt_gt = ctx->single.dev.GT.fmt;
     res->idx16 = (ctx->single.dev.A.idx16 ? 1 : 0) | (ctx->single.dev.G.idx16 ? 2 : 0) |
                  (ctx->single.dev.GT.idx16 ? 4 : 0);
-    res->temporal = ctx->single.dev.A.temporal | (ctx->single.dev.G.temporal << 1) |
-                    (ctx->single.dev.GT.temporal << 2);
+    res->temporal = load_policy(ctx);
     res->rows_per_lane_gt = ctx->single.dev.GT.rpl;
     res->loads_in_flight_a = ctx->set_main.L.uw_a;
   }
