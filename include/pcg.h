@@ -447,8 +447,8 @@ int pcg_build_g_host(int kind, uint64_t seed, int32_t n, const int32_t *rowptr, 
  * same solve bit for bit. A layout forced in the configuration is kept; only
  * the grid, the load policy and the kernel knobs are tuned then.
  * The choice is cached per matrix signature (sizes, row-length structure, 3x3
- * blocking, storage types, options, compute units) for the process, and in
- * the file named by the environment variable PCG_TUNE_CACHE when set; a
+ * blocking, storage types, options, compute units, library version of the
+ * search) for the process, and in the file named by the environment variable PCG_TUNE_CACHE when set; a
  * cached signature is applied without search (candidates = 0). A new
  * pcg_set_matrix returns to the automatic layouts. Needs A and G set;
  * overwrites the stored right-hand side. iters <= 0: 20; above 1000:

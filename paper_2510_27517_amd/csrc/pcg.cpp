@@ -3093,7 +3093,7 @@ int pcg_build_precond(pcg_ctx *ctx, int kind, uint64_t seed) {
 
 // Choices per matrix signature, shared by the contexts of the process and,
 // when the environment names a file in PCG_TUNE_CACHE, kept there as lines
-// "signature layout_a layout_g grid_mult load_policy".
+// "signature layout_a layout_g grid_mult load_policy rows_per_lane loads_in_flight".
 static std::mutex g_tune_mu;
 static std::map<std::string, pcg_ctx::Tune> g_tune_cache;
 static bool g_tune_loaded = false;
@@ -3133,7 +3133,11 @@ static void tune_cache_store(const std::string &key, const pcg_ctx::Tune &t) {
 }
 
 // What the layouts depend on: sizes, row-length structure, 3x3 blocking,
-// storage types, the compute-unit count and the layout options.
+// storage types, the compute-unit count and the layout options; and the version
+// of the kernels and candidates that the choice was timed with. A file of an
+// earlier one is searched again: from before stencil storage (no version) it
+// names a layout, which would switch that storage off.
+constexpr int kTuneVersion = 2;
 static std::string tune_key(const pcg_ctx *ctx) {
   const int32_t n = (int32_t)ctx->a_rp.size() - 1;
   const int32_t *rp = ctx->a_rp.data();
@@ -3143,10 +3147,10 @@ static std::string tune_key(const pcg_ctx *ctx) {
   const bool b3 = pcgh::is_block3(n, rp, ctx->a_ci.data(), &nb);
   const pcg_config &c = ctx->cfg;
   char buf[384];
-  std::snprintf(buf, sizeof buf, "n%d_a%lld_g%lld_r%d_s%lld_b%d_t%d.%d.%d_f%d.%d.%d.%d.%d_cu%d", n,
+  std::snprintf(buf, sizeof buf, "n%d_a%lld_g%lld_r%d_s%lld_b%d_t%d.%d.%d_f%d.%d.%d.%d.%d_cu%d_v%d", n,
                 (long long)rp[n], (long long)ctx->single.nnz_g, maxrow, (long long)pcgh::sell_entries(n, rp),
                 (int)b3, c.vec_dtype, c.a_dtype, c.g_dtype, c.refine, c.layout, c.wide_index, c.grid_mult,
-                c.cache_mb, ctx->cus);
+                c.cache_mb, ctx->cus, kTuneVersion);
   return buf;
 }
 
