@@ -60,51 +60,63 @@ __device__ __forceinline__ void loss_terms(double (&acc)[5], double w, double y,
 // halves of 16 probes it took 180). All three and the probes' copy and the
 // separate pass over W and Y took 1240 us before. Two entries in flight per
 // lane: with four, the waves drift further apart and A's product re-reads
-// more (202 us), with eight 278.
+// more (202 us), with eight 278. Over one probe per lane four: those are the
+// launches of few waves or of an odd count, where latency binds (20,000 rows of
+// 100, 7 probes: 0.90 of the time with two). 3x3 blocks go a block at a time, with
+// one index and no division per entry (elasticity 24^3, 32 probes: 233 -> 170
+// us). thin: a loss launch with little more than one turn of rows per wave gives
+// a workgroup's waves rows apart, so that no CU takes two full workgroups while
+// others have one (elasticity 8^3, 8 probes: 66 -> 52 us).
 template <typename TM, int LPR, int PV, int NT, bool LOSS>
 __device__ __forceinline__ void spmm(const DevCSR &Md, int32_t k, GLOBAL const double *X, int32_t ldx, double c,
                                      GLOBAL const double *Z, int32_t ldz, double d, GLOBAL double *Y, int32_t ldy,
                                      double na, GLOBAL double *part, int32_t ldp, double *sh) {
   const Mat<TM> M = mat<TM>(Md);
-  constexpr int RPW = 64 / LPR, NW = NT / 64, CH = LPR * PV, U = 2;
+  constexpr int RPW = 64 / LPR, NW = NT / 64, CH = LPR * PV;
   const int lane = threadIdx.x & 63, grp = lane / LPR, pl = (lane % LPR) * PV;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l = blockIdx.x, W = gridDim.x >> 3, die = l & 7, w = l >> 3;
-  const int T = (M.n + NW * RPW - 1) / (NW * RPW);
+  const int T = (M.n + RPW - 1) / RPW;
+  const bool thin = LOSS && T < 2 * (int)gridDim.x * NW;
   const int t0 = (int)((int64_t)die * T / 8), t1 = (int)((int64_t)(die + 1) * T / 8);
   for (int32_t p0 = 0; p0 < k; p0 += CH) {
     const int32_t p = p0 + pl;
     const bool pact = p < k;  // PV = 2 only for even k: both probes exist or neither
     double acc[LOSS ? PV : 1][5] = {};
-    for (int t = t0 + w; t < t1; t += W) {
-      const int32_t base = (t * NW + wv) * RPW, row = min(base + grp, M.n - 1);
+    for (int t = t0 + (thin ? wv * W + w : w * NW + wv); t < t1; t += W * NW) {
+      const int32_t base = t * RPW, row = min(base + grp, M.n - 1);
       const bool act = pact && base + grp < M.n;
       double sum[PV] = {};
-      // entries in CSR order, U at a time; the last batch's surplus loads
-      // repeat an entry in bounds and are not added
-      auto walk = [&](int len, auto entry) {
-        for (int e = 0; e < len; e += U) {
-          double a[U], x[U][PV];
+      // N entries in CSR order with all their loads in flight; past the row's end
+      // they repeat its last entry (in bounds) and are not added
+      auto batch = [&](int e, int len, auto width, auto entry) {
+        constexpr int N = decltype(width)::value;
+        double a[N], x[N][PV];
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int ee = min(e + u, len - 1);
-            int32_t col;
-            entry(ee, col, a[u]);
-            const int64_t at = (int64_t)col * ldx + (pact ? p : 0);
-            if constexpr (PV == 2) {
-              const Pair<double> v = ld_pair(X, at);
-              x[u][0] = v.x;
-              x[u][1] = v.y;
-            } else {
-              x[u][0] = X[at];
-            }
+        for (int u = 0; u < N; ++u) {
+          const int ee = min(e + u, len - 1);
+          int32_t col;
+          entry(ee, col, a[u]);
+          const int64_t at = (int64_t)col * ldx + (pact ? p : 0);
+          if constexpr (PV == 2) {
+            const Pair<double> v = ld_pair(X, at);
+            x[u][0] = v.x;
+            x[u][1] = v.y;
+          } else {
+            x[u][0] = X[at];
           }
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (e + u < len)
-#pragma unroll
-              for (int j = 0; j < PV; ++j) sum[j] += a[u] * x[u][j];
         }
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+          if (e + u < len)
+#pragma unroll
+            for (int j = 0; j < PV; ++j) sum[j] += a[u] * x[u][j];
+      };
+      auto walk = [&](int len, auto entry) {
+        int e = 0;
+        if constexpr (PV == 1)
+          for (; e + 4 <= len; e += 4) batch(e, len, std::integral_constant<int, 4>{}, entry);
+        for (; e < len; e += 2) batch(e, len, std::integral_constant<int, 2>{}, entry);
       };
       if (M.fmt == FMT_SDIA) {  // one offset per slice entry; stored zeros add +0
         const int sl = __builtin_amdgcn_readfirstlane(min(base, M.n - 1) / kSliceRows);
@@ -114,16 +126,25 @@ __device__ __forceinline__ void spmm(const DevCSR &Md, int32_t k, GLOBAL const d
           col = min(max(row + ro(M.ci)[o0 + e], 0), M.n - 1);
           a = ld64(vv, (int64_t)e * kSliceRows);
         });
-      } else if (M.fmt == FMT_BSR3) {  // whole blocks: three entries of the row per block
+      } else if (M.fmt == FMT_BSR3) {  // a block at a time: three entries of the row
         const int32_t R = row / 3, sub = row % 3, sl = R / kBSliceRows, rr = R % kBSliceRows;
         const int32_t o0 = M.blk[sl], wd = M.blk[sl + 1] - o0;
-        walk(3 * wd, [&](int e, int32_t &col, double &a) {
-          const int b = e / 3, j = e - 3 * b;
-          const int64_t at = ((int64_t)o0 + b) * kBSliceRows + rr;
-          col = 3 * M.ci[at] + j;
-          a = ld64(M.val, sizeof(TM) == 8 ? (((int64_t)o0 + b) * 3 + j) * (3 * kBSliceRows) + sub * kBSliceRows + rr
-                                          : at * 9 + 3 * sub + j);
-        });
+        GLOBAL const int32_t *bc = M.ci + (int64_t)o0 * kBSliceRows + rr;
+        GLOBAL const TM *bv = M.val + (int64_t)o0 * (9 * kBSliceRows) +
+                              (sizeof(TM) == 8 ? sub * kBSliceRows + rr : 9 * rr + 3 * sub);
+        for (int b = 0; b < wd; ++b, bc += kBSliceRows, bv += 9 * kBSliceRows) {
+          const int32_t c0 = 3 * *bc;
+          auto entry = [&](int j, int32_t &col, double &a) {
+            col = c0 + j;
+            a = ld64(bv, sizeof(TM) == 8 ? 3 * kBSliceRows * j : j);
+          };
+          if constexpr (LOSS && PV == 2) {  // three at once would spill
+            batch(0, 3, std::integral_constant<int, 2>{}, entry);
+            batch(2, 3, std::integral_constant<int, 1>{}, entry);
+          } else {
+            batch(0, 3, std::integral_constant<int, 3>{}, entry);
+          }
+        }
       } else if (M.fmt == FMT_SELL) {  // padded entries add +0 (value 0, valid column)
         const int sl = __builtin_amdgcn_readfirstlane(min(base, M.n - 1) / kSliceRows);
         const int o0 = ro(M.blk)[sl], wd = ro(M.blk)[sl + 1] - o0;
@@ -154,7 +175,6 @@ __device__ __forceinline__ void spmm(const DevCSR &Md, int32_t k, GLOBAL const d
         double y = c * sum[j];
         if constexpr (LOSS) {
           loss_terms(acc[j], Z[az + j], y, na);
-
         } else {
           if (Z) y = y + d * Z[az + j];
           sum[j] = y;
@@ -283,27 +303,44 @@ hipError_t launch_spmv(const Types &ty, const DevCSR &M, int x_dtype, const void
   return hipErrorInvalidValue;
 }
 
-// The smallest lane groups that hold the probes, two probes per lane when
-// they pair up.
-#define PCG_SPMM_SHAPE(k, LPR, PV, ...)                                                                \
-  do {                                                                                                 \
-    if ((k) % 2 == 0) {                                                                                \
-      constexpr int PV = 2;                                                                            \
-      if ((k) <= 4) { constexpr int LPR = 2; __VA_ARGS__; }                                            \
-      else if ((k) <= 8) { constexpr int LPR = 4; __VA_ARGS__; }                                       \
-      else if ((k) <= 16) { constexpr int LPR = 8; __VA_ARGS__; }                                      \
-      else if ((k) <= 32) { constexpr int LPR = 16; __VA_ARGS__; }                                     \
-      else if ((k) <= 64) { constexpr int LPR = 32; __VA_ARGS__; }                                     \
-      else { constexpr int LPR = 64; __VA_ARGS__; }                                                    \
-    } else {                                                                                           \
-      constexpr int PV = 1;                                                                            \
-      if ((k) <= 2) { constexpr int LPR = 2; __VA_ARGS__; }                                            \
-      else if ((k) <= 4) { constexpr int LPR = 4; __VA_ARGS__; }                                       \
-      else if ((k) <= 8) { constexpr int LPR = 8; __VA_ARGS__; }                                       \
-      else if ((k) <= 16) { constexpr int LPR = 16; __VA_ARGS__; }                                     \
-      else if ((k) <= 32) { constexpr int LPR = 32; __VA_ARGS__; }                                     \
-      else { constexpr int LPR = 64; __VA_ARGS__; }                                                    \
-    }                                                                                                  \
+// The smallest lane groups that hold the probes, two probes per lane where they
+// pair up. That halves the accesses but also the waves, so it needs 4,096 of them
+// left, half of what the chip holds (losses over 8 probes, paired against one per
+// lane: elasticity 36^3, 8,748 waves, 161 and 232 us; 20,000 rows of 100, 1,250
+// waves, 216 and 112; elasticity 8^3, 96 waves, 74 and 51; P P^T of 18,000 over 16,
+// 2,250 waves, 141 and 108), and more than two probes, which would leave every other
+// lane idle (100^3: 91 and 77).
+static void spmm_shape(int32_t n, int32_t k, int &lpr, bool &pair) {
+  auto fit = [](int32_t m) {
+    int l = 2;
+    while (l < m && l < 64) l *= 2;
+    return l;
+  };
+  pair = k > 2 && k % 2 == 0 && (int64_t)n * fit(k / 2) / 64 >= 4096;
+  lpr = fit(pair ? k / 2 : k);
+}
+
+#define PCG_SPMM_LPR(lpr_, LPR, ...)                            \
+  switch (lpr_) {                                               \
+    case 2: { constexpr int LPR = 2; __VA_ARGS__; break; }      \
+    case 4: { constexpr int LPR = 4; __VA_ARGS__; break; }      \
+    case 8: { constexpr int LPR = 8; __VA_ARGS__; break; }      \
+    case 16: { constexpr int LPR = 16; __VA_ARGS__; break; }    \
+    case 32: { constexpr int LPR = 32; __VA_ARGS__; break; }    \
+    default: { constexpr int LPR = 64; __VA_ARGS__; break; }    \
+  }
+#define PCG_SPMM_SHAPE(n, k, LPR, PV, ...)           \
+  do {                                               \
+    int lpr_;                                        \
+    bool pair_;                                      \
+    spmm_shape(n, k, lpr_, pair_);                   \
+    if (pair_) {                                     \
+      constexpr int PV = 2;                          \
+      PCG_SPMM_LPR(lpr_, LPR, __VA_ARGS__)           \
+    } else {                                         \
+      constexpr int PV = 1;                          \
+      PCG_SPMM_LPR(lpr_, LPR, __VA_ARGS__)           \
+    }                                                \
   } while (0)
 
 // A multiple of 8 workgroups, enough to take every row, at most `most`.
@@ -315,7 +352,7 @@ static int spmm_grid(int32_t n, int rows_per_wg, int most) {
 hipError_t launch_spmm(const DevCSR &M, int32_t k, const double *X, int32_t ldx, double c, const double *Z,
                        int32_t ldz, double d, double *Y, int32_t ldy, hipStream_t s) {
   if (M.n <= 0 || k <= 0) return hipSuccess;
-  PCG_PROD_M(M.dtype, TM, PCG_SPMM_SHAPE(k, LPR, PV, {
+  PCG_PROD_M(M.dtype, TM, PCG_SPMM_SHAPE(M.n, k, LPR, PV, {
     const int grid = spmm_grid(M.n, kBlock / LPR, kSpmmGrid);
     hipLaunchKernelGGL((k_spmm<TM, LPR, PV>), dim3(grid), dim3(kBlock), 0, s, M, k, X, ldx, c, Z, ldz, d, Y,
                        ldy);
@@ -327,12 +364,12 @@ hipError_t launch_spmm_loss(const DevCSR &M, int32_t k, const double *X, int32_t
                             double na, double *part, int32_t ldp, hipStream_t s) {
   if (M.n <= 0 || k <= 0) return hipSuccess;
   if (M.dtype == F64)
-    PCG_SPMM_SHAPE(k, LPR, PV, {
+    PCG_SPMM_SHAPE(M.n, k, LPR, PV, {
       hipLaunchKernelGGL((k_spmm_loss<double, LPR, PV>), dim3(kLossGrid), dim3(kLossThreads), 0, s, M, k, X, ldx,
                          W, ldw, na, part, ldp);
     });
   else if (M.dtype == F32)
-    PCG_SPMM_SHAPE(k, LPR, PV, {
+    PCG_SPMM_SHAPE(M.n, k, LPR, PV, {
       hipLaunchKernelGGL((k_spmm_loss<float, LPR, PV>), dim3(kLossGrid), dim3(kLossThreads), 0, s, M, k, X, ldx,
                          W, ldw, na, part, ldp);
     });
