@@ -814,7 +814,7 @@ struct pcg_ctx {
   std::map<int, hipGraphExec_t> graphs;    // key: iters*4 + parity of the first iteration*2 + replace_first
   std::map<int, hipGraphExec_t> graphs_x;  // the same for the escalated FP64 inner solves
   HostSet set_x;
-  hipEvent_t ev[2] = {nullptr, nullptr}, t0 = nullptr, t1 = nullptr;
+  hipEvent_t t0 = nullptr, t1 = nullptr;
 
   // batching / serving
   DevPool pool;
@@ -2711,8 +2711,6 @@ int pcg_create(const pcg_config *cfg, pcg_ctx **out) {
   if (hipHostMalloc((void **)&ctx->h_states, sizeof(State) * 2 * kDirCap, hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void **)&ctx->h_init, sizeof(State) * 2, hipHostMallocDefault) != hipSuccess)
     return fail(PCG_EDEVICE);
-  for (auto &e : ctx->ev)
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return fail(PCG_EDEVICE);
   if (hipEventCreate(&ctx->t0) != hipSuccess || hipEventCreate(&ctx->t1) != hipSuccess) return fail(PCG_EDEVICE);
   if (ctx->da.get((void **)&ctx->d_dir, sizeof(SysDev) * kDirCap) != hipSuccess ||
       ctx->da.get((void **)&ctx->d_states, sizeof(State) * 2 * kDirCap) != hipSuccess)
@@ -2757,8 +2755,6 @@ void pcg_destroy(pcg_ctx *ctx) {
   free_set(ctx, ctx->set_tmp64);
   free_sys(ctx, ctx->single);
   ctx->pool.reset();
-  for (auto &e : ctx->ev)
-    if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : ctx->step_ev)
     if (e) (void)hipEventDestroy(e);
   if (ctx->t0) (void)hipEventDestroy(ctx->t0);
