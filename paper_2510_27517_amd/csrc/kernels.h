@@ -289,11 +289,6 @@ int32_t wgs_max_n(const Types &ty, int32_t na, int32_t ng);  // 0: not this kind
 size_t wgs_lds_bytes(int vec_dtype, int32_t n, int32_t pad);
 hipError_t launch_wgs(const Types &ty, const WgsArgs &P, const State &S0, hipStream_t s);
 
-// x += alpha d_{iter-1} if an update is still pending (alpha != 0), then
-// alpha = 0. The G-kernel applies every update itself and leaves alpha = 0, so
-// this only matters for states written by the host.
-hipError_t launch_finalize(const Types &ty, const LaunchSet &L, hipStream_t s);
-
 // ||b||^2, tol*||b|| into st[0]; ZERO_B status when b = 0.
 hipError_t launch_norm_b(const Types &ty, const LaunchSet &L, hipStream_t s);
 

@@ -95,20 +95,6 @@ __global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_resid(const SysDev *__
 }
 
 template <typename TV>
-__global__ __launch_bounds__(kBlock) void k_finalize(const SysDev *__restrict__ dir, const int2 *__restrict__ map) {
-  const int2 m = map[blockIdx.x];
-  const SysDev &D = dir[m.x];
-  GLOBAL const State &S = gl(D.st)[0];
-  const TV al = (TV)S.alpha;
-  if (al == (TV)0) return;
-  GLOBAL TV *__restrict__ x = gl((TV *)D.x);
-  GLOBAL const TV *__restrict__ dc = gl((const TV *)(((S.iter - 1) & 1) ? D.d1 : D.d0));
-  int64_t i0, i1;
-  ew_rows(D.n, m.y, D.A.grid, i0, i1);
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += kBlock) x[i] = x[i] + al * dc[i];
-}
-
-template <typename TV>
 __global__ __launch_bounds__(kBlock) void k_zero_dirs(const SysDev *__restrict__ dir, const int2 *__restrict__ map,
                                                       int zero_x) {
   const int2 m = map[blockIdx.x];
@@ -150,11 +136,6 @@ __global__ __launch_bounds__(kBlock) void k_outer(const SysDev *__restrict__ dir
 }
 
 // One thread per system of the set.
-__global__ void k_state_clear_alpha(const SysDev *__restrict__ dir, const int32_t *__restrict__ set, int nset) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < nset) gl(dir[set[k]].st)[0].alpha = 0.0;
-}
-
 __global__ void k_state_restart(const SysDev *__restrict__ dir, const int32_t *__restrict__ set, int nset) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nset) return;
@@ -642,15 +623,6 @@ hipError_t launch_resid(const Types &ty, const LaunchSet &L, int slot_sel, bool 
     return hipErrorInvalidValue;
   }
   if (reduce) hipLaunchKernelGGL(k_reduce_state, dim3(L.nset), dim3(kBlock), 0, s, L.dir, L.set, 1);
-  return hipGetLastError();
-}
-
-hipError_t launch_finalize(const Types &ty, const LaunchSet &L, hipStream_t s) {
-  if (L.nA == 0) return hipSuccess;
-  PCG_DISPATCH_V(ty.vec, TV, {
-    hipLaunchKernelGGL((k_finalize<TV>), dim3(L.nA), dim3(kBlock), 0, s, L.dir, L.mapA);
-  });
-  hipLaunchKernelGGL(k_state_clear_alpha, dim3((L.nset + 255) / 256), dim3(256), 0, s, L.dir, L.set, L.nset);
   return hipGetLastError();
 }
 

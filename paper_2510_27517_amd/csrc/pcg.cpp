@@ -2509,10 +2509,9 @@ int progress(pcg_ctx *ctx, int iters) {
   if (done_slots.empty()) return PCG_OK;
   phase.reset();
   phase.emplace(ctx, &pcg_batch_stats::host_retire_ms);
-  // finish the stopped systems: any pending x update, true residual
+  // finish the stopped systems (the G-kernel has applied their last x update): true residual
   HostSet &hs = ctx->set_done;
   if ((rc = build_set(ctx, hs, done_slots))) return rc;
-  HIPCHK(pcgk::launch_finalize(ctx->ty, hs.L, s));
   HIPCHK(pcgk::launch_resid(ctx->ty, hs.L, 0, false, true, false, s));
   HIPCHK(hipMemcpyAsync(ctx->h_states, ctx->d_states, sb, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
