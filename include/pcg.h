@@ -110,7 +110,8 @@ typedef struct {
                         kernel's partial sums reads all of them, so fewer, fuller workgroups pay) */
   int mem_budget_mb; /* device memory pool for batched / served systems, MiB (0: half the free memory at first use) */
   int layout;        /* storage of A, G, G^T: PCG_LAYOUT_AUTO (default), _CSR, _SELL, _BSR3 or _SDIA */
-  int g_device;      /* 1: FSAI factored on the device (one wave per row; same arithmetic as the host
+  int g_device;      /* 1: FSAI factored on the device (one wave per row, one thread per row where every
+                        tril row has at most 8 entries; same arithmetic as the host
                         builder, bit-identical G): in pcg_build_precond(PCG_G_FSAI), and for batched
                         systems with FSAI at admission (the host lays out only the patterns; F16 G
                         is built on the host). Falls back to the host builder for tril rows longer
@@ -290,8 +291,9 @@ int pcg_matvec(pcg_ctx *ctx, int op, const double *x, double *y, int on_device);
  * FP64, host or device memory (on_device), borrowed for the call; sai, l2,
  * cs: host arrays of k doubles, each may be NULL. Products run in FP64 on the
  * stored values (rounded to their storage types); each row is summed in CSR
- * order. Uses 3 n k doubles of device scratch, allocated at the first call
- * that needs more and kept by the context until pcg_destroy.
+ * order. Uses 2 n k + 2563 k doubles of device scratch, n k more for probes in
+ * host memory (those in device memory are read where they are), allocated at
+ * the first call that needs more and kept by the context until pcg_destroy.
  * PCG_EINVAL (k < 1, null W), PCG_ESTATE (A or G unset), PCG_ENOMEM. */
 int pcg_sai_loss(pcg_ctx *ctx, int32_t k, const double *W, int on_device, double *sai, double *l2, double *cs);
 
@@ -443,8 +445,8 @@ int pcg_build_g_host(int kind, uint64_t seed, int32_t n, const int32_t *rowptr, 
  * (8 or 4; stencil storage has neither knob), and keeps the fastest (a
  * candidate must beat the current best by 3%).
  * The matrices are laid out again with the same values, so products stay
- * bit-identical, and inner products are exact: every candidate gives the
- * same solve bit for bit. A layout forced in the configuration is kept; only
+ * bit-identical, and inner products do not depend on how they are split:
+ * every candidate gives the same solve bit for bit. A layout forced in the configuration is kept; only
  * the grid, the load policy and the kernel knobs are tuned then.
  * The choice is cached per matrix signature (sizes, row-length structure, 3x3
  * blocking, storage types, options, compute units, library version of the

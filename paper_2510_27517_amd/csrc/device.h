@@ -1,6 +1,6 @@
 // Device-side building blocks shared by the gfx950 kernels: matrix access in
-// every storage layout (rows summed left to right in CSR order), exact inner
-// products, and the placement of a system's work on workgroups. The layouts
+// every storage layout (rows summed left to right in CSR order), inner
+// products in double-double sums, and the placement of a system's work on workgroups. The layouts
 // are described at DevCSR.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -816,9 +816,9 @@ __device__ __forceinline__ bool for_rows_h(const Mat<TM> &M, int l, int G, TACC 
 
 // ---- inner products
 //
-// Every dot product and norm is its exact value rounded once to FP64, the
-// value that does not depend on how the sum is split over lanes, waves and
-// workgroups. Each lane accumulates its products as an unevaluated double-
+// Every dot product and norm is, up to the bound below, its exact value rounded
+// once to FP64, the value that does not depend on how the sum is split over lanes,
+// waves and workgroups. Each lane accumulates its products as an unevaluated double-
 // double hi + lo (the product's rounding error from an FMA, the additions'
 // from TwoSum: Ogita, Rump and Oishi's Dot2); partial sums are combined as
 // double-doubles in any order and rounded once at the end. The result is the

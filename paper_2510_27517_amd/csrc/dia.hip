@@ -10,8 +10,8 @@
 // follows from its number, so a tile's loads are all issued at once.
 //
 // Rows are summed left to right in column order from zero, as in every other
-// layout, and inner products are exact, so a solve has the same bits as
-// through the general kernels. (Diagonal entries that a row does not have are
+// layout, and inner products do not depend on how they are split (up to the
+// bound in device.h), so a solve has the same bits as through the general kernels. (Diagonal entries that a row does not have are
 // stored zeros: each adds +0 to a sum that can never be -0.)
 //
 // Built with floating-point contraction off, like every kernel here.

@@ -4,9 +4,9 @@
 // each the registers and the schedule of the others, which never meet in a
 // single system's launch, so a change for one layout moved the others; built
 // apart, each takes what is best for it (per iteration, FP64, with the loads of
-// single.hip: 3x3 blocks of elasticity 40^3 60.5 -> 59.9 us, a graph of 150,001
-// 27.1 -> 26.4 and of 600,001 55.0 -> 51.4, irregular rows of 18,000 23.5 -> 22.5;
-// FP32 with a BF16 G: 36.2 -> 35.9, 21.9 -> 21.0, 46.9 -> 45.3, 24.1 -> 23.3).
+// single.hip: 3x3 blocks of elasticity 40^3 60.5 -> 59.8 us, a graph of 150,001
+// 27.1 -> 26.6 and of 600,001 55.0 -> 51.7, irregular rows of 18,000 23.5 -> 22.4;
+// FP32 with a BF16 G: 36.2 -> 36.3, 21.9 -> 21.3, 46.9 -> 43.9, 24.1 -> 23.5).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cmath>

@@ -260,9 +260,10 @@ hipError_t launch_dia_build(const DevCSR &M, const DiaOp &o, int32_t *flag, hipS
 // the kernel; no host round trip, no other launch). The states are set up as
 // for the iteration kernels (tol, maxit, eps, rr_period, x holding x0); on
 // return st[0] holds what the iteration kernels and the true-residual kernel
-// would leave: iter, status, rr, tt, bb, tol_nb, true_rr, restarts, done = 1.
-// Every row and every inner product is computed as by the iteration kernels
-// (same row sums; exact inner products), so the results are theirs bit for
+// would leave: iter, status, rr, tt, bb, tol_nb, true_rr (after a breakdown too),
+// restarts, done = 1.
+// Every row is computed as by the iteration kernels, and inner products do not
+// depend on how they are split (device.h), so the results are theirs bit for
 // bit. For small systems, where three launches per iteration dominate.
 // Storage types it is built for: all FP64, or FP32 vectors and A with an
 // FP32, BF16 or FP16 G (others: hipErrorInvalidValue).
@@ -304,8 +305,8 @@ hipError_t launch_state_restart(const LaunchSet &L, hipStream_t s);
 
 // y = M x for one stored matrix, rows summed in the vector type ty.vec; x and
 // y in FP64 or, for FP32 vectors, one of them in FP32 (converted at the gather
-// and at the store). z set (FP64): y = a (M x) + b z, in the vector type. y may
-// be z; it must not overlap x.
+// and at the store). z set (FP64): y = a (M x) + b z, in the vector type. y must
+// overlap neither x nor z.
 hipError_t launch_spmv(const Types &ty, const DevCSR &M, int x_dtype, const void *x, int y_dtype, void *y,
                        const double *z, double a, double b, hipStream_t s);
 
@@ -327,7 +328,7 @@ hipError_t launch_refine_update(int32_t n, double *x64, const void *c, int c_dty
 // of the host builder in the same order. err[0] = 1 on a non-positive pivot.
 // mmax (the longest tril row) sizes the LDS: at most kFsaiMaxRow.
 constexpr int kFsaiMaxRow = 80;
-constexpr int kFsaiShortRow = 8;  // longest tril row that one thread factors (36 KiB of LDS per wave)
+constexpr int kFsaiShortRow = 8;  // longest tril row that one thread factors (38 KiB of LDS per wave)
 hipError_t launch_fsai_rows(const int32_t *rp, const int32_t *ci, const double *v, const int32_t *dpos,
                             const int32_t *lrp, int32_t n, int32_t mmax, double *lv, int32_t *err, int grid,
                             hipStream_t s);

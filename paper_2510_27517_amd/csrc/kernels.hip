@@ -557,8 +557,12 @@ static inline int ew_grid(int64_t n) {
 // sliced diagonals (the kernels here hold their two-row walk), and not CSR of
 // long rows, where a block holds few rows and the threads that sum them bound
 // it: at 470 entries per row (72,000 rows) the A-kernel takes 237 us here against
-// 255 in FP64 and the G^T-kernel (237 per row) 152 against 167 in FP32; at 145
-// and 76 per row (40,000 rows) an iteration takes 92.5 us against 91.4 there.
+// 255 in FP64 and the G^T-kernel (237 per row) 152 against 167 in FP32. The line
+// lies where the two begin to part; below it they stay within 5% of each other in
+// each kernel and type (an iteration with G on A's pattern, here and there: 40,000
+// rows of 145 137.4 and 140.9 us in FP64, 119.4 and 118.8 in FP32, of 175 159.7 and
+// 159.1, 136.4 and 134.5; 72,000 rows of 190 355.8 and 347.9, 284.9 and 286.7), above
+// it by up to 9% (72,000 rows of 300: 567.8 and 568.5, 437.4 and 448.9).
 static bool one_layout(const DevCSR &M) {
   return M.fmt != FMT_SDIA && !(M.fmt == FMT_CSR && (int64_t)M.nnz > (int64_t)192 * M.n);
 }

@@ -1040,10 +1040,12 @@ double placed_bytes(const pcgk::DevCSR &M) {
 // loads, so that they stay in the memory-side cache (cfg.cache_mb, default
 // 256 MB) from one iteration to the next, and which stream past it. All three
 // when the matrices and the 8 iteration vectors fit in 105% of the cache: a
-// little over its size most of them still stay (FP64, per iteration, all
-// against A alone: elasticity 40^3, 272 MB, 61.5 us against 67.3; a graph of
-// 800,001, 243 MB, 61.0 against 70.8), far over it nothing does (42^3, 315 MB,
-// 90.9 against 84.2; 44^3 100.7 against 89.0). Else the first of A alone, G and
+// little over its size most of them still stay, far over it nothing does (per
+// iteration, all against A alone; FP64: elasticity 40^3, 272 MB, 60.8 us against 66.3,
+// graphs of 900,001, 273 MB, 74.1 against 78.7, of 960,001, 291 MB, 83.6 against 83.9,
+// elasticity 41^3, 293 MB, 84.5 against 81.4; FP32 with a BF16 G: elasticity 54^3 79.8
+// against 81.9, graphs of 1,600,001 100.0 against 98.9, of 1,700,001 107.4
+// against 101.7). Else the first of A alone, G and
 // G^T together, G alone that fits in 75% (the vectors and the other matrices
 // stream around it); else none. The FP64 view of A under refinement always
 // streams.
@@ -1081,8 +1083,8 @@ bool use_solve_wg(const pcg_ctx *ctx, const Types &ty, int32_t n, bool batch = f
 // registers: stencils of few diagonals and at most 2048 rows, as far as they
 // fit in registers, unless pcg_config.wg_max_n sets another bound than its
 // default. Per iteration, the whole call, FP64: 8^2 rows 2.7 us against 10.9
-// with the matrices in memory and 19 for three launches; 45^2 3.3 against
-// 19 and 12.5; 10^3 4.0 against 19 and 17. It is ahead wherever it fits.
+// with the matrices in memory and 18 for three launches; 45^2 3.3 against
+// 19 and 11.5; 10^3 4.1 against 19 and 16. It is ahead wherever it fits.
 bool use_wgs(const pcg_ctx *ctx, const Types &ty) {
   const Sys &S = ctx->single;
   const int cf = ctx->cfg.wg_max_n;
@@ -3503,9 +3505,9 @@ static hipError_t enqueue_losses(pcg_ctx *ctx, int32_t k, const double *W, doubl
   };
   // Large blocks go in chunks of at most 32 columns, an odd last one of more
   // than 15 without its last column, which follows alone: two columns per lane
-  // need an even count, and one per lane is slow (96^3, 33 probes: 555 us
-  // against 1302 in one piece, 31: 545 against 750; 7 in one piece: 168
-  // against 195). Small ones go whole: there each launch costs more than that.
+  // need an even count, and one per lane is slow (96^3, 33 probes: 537 us
+  // against 1255 in one piece, 31: 529 against 727; 7 in one piece: 158
+  // against 188). Small ones go whole: there each launch costs more than that.
   const bool chunks = 8.0 * S.n * k > 32e6;
   for (int32_t p = 0, m = 0; p < k; p += m) {
     m = chunks ? std::min(32, k - p) : k;

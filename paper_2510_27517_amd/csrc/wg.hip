@@ -1,5 +1,5 @@
 // One-workgroup solver: a whole PCG solve of a small system in one launch
-// (the phases, row sums and exact inner products of the iteration kernels).
+// (the phases, row sums and inner products of the iteration kernels).
 // Built with floating-point contraction off, like every kernel here.
 #include <hip/hip_runtime.h>
 #include <cstdint>

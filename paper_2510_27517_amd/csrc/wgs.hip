@@ -6,8 +6,8 @@
 // entries of x, r and d in registers for the whole solve; only d, r and t, the
 // vectors that neighbouring rows gather, go through LDS, and q, s and the
 // gathered r_i - alpha q are formed once by their own row. Every row and every
-// inner product is computed as by the iteration kernels (same order, exact
-// sums), so the result is theirs bit for bit. A diagonal's entry that a row
+// inner product is computed as by the iteration kernels (rows in the same order,
+// sums that do not depend on their split), so the result is theirs bit for bit. A diagonal's entry that a row
 // does not have is a zero times a finite value (LDS is padded with zeros on
 // both sides), which adds +0 to a sum that can never be -0.
 //
@@ -15,8 +15,8 @@
 // about as much as four of its rows' work, and one workgroup's waves share
 // four SIMDs, so few waves with several rows each are best until the values no
 // longer fit in registers (launch_wgs). Inside the kernel an iteration takes
-// 1.1 us at 64 rows (one wave, no barrier), 1.5 at 256, 2.3 at 1024 and 3.1 at
-// 2025 (2D FP64; 3D at 1000 rows 3.0), against 8.9 at 64 and 19 at 1024 rows
+// 1.1 us at 64 rows (one wave, no barrier), 1.6 at 256, 2.3 at 1024 and 3.0 at
+// 2025 (2D FP64; 3D at 1000 rows 3.2), against 8.9 at 64 and 19 at 1024 rows
 // when the matrices are read from memory in every iteration.
 //
 // Built with floating-point contraction off, like every kernel here.
