@@ -21,6 +21,9 @@ def test_times_every_policy_once_and_no_knob_without_effect(gpu_lib):
         want = s.solve(b, tol=1e-8, maxit=5000)
         t = s.autotune(10)
         got = s.solve(b, tol=1e-8, maxit=5000)
-    assert t["candidates"] == 1 + 3 * 3 + 2 + 3, t
-    assert t["temporal"] in (0, 1, 6, 7)
+    if t["layout_a"] == t["layout_g"] == pcg.LAYOUT_AUTO:
+        assert t["candidates"] == 1 + 3 * 3 + 2 + 3, t
+        assert t["temporal"] in (0, 1, 6, 7)
+    else:  # a layout asked for was timed faster: no stencil storage, every subset and both knobs
+        assert t["candidates"] == 1 + 3 * 3 + 2 + 7 + 2, t
     assert got.iters == want.iters and np.array_equal(got.x, want.x)
