@@ -171,21 +171,23 @@ __device__ __forceinline__ TACC lds_row_sum(const TACC *lds, int a, int e, TACC 
 // Which is faster depends on the kernel's types: see the kernels' US.
 template <typename TACC, int U, bool NT, typename TM, typename Gather>
 __device__ __forceinline__ void stage_products(const Mat<TM> &M, int c0, int c1, TACC *lds, Gather gather) {
-  // unsigned: nonzeros number up to 2^31 - 1, and a round's step past the last
-  // of them must not wrap below zero
-  const uint32_t end = (uint32_t)c1;
+  // entries count from the block's first: nonzeros number up to 2^31 - 1, and a
+  // round's step past the last of them must not wrap below zero (counted from the
+  // matrix's first in unsigned, 72,000 rows of 470 took 582 us per iteration in
+  // FP64 and 434 in FP32 against 561 and 414)
+  const int m = c1 - c0;
   if constexpr (U <= 1) {
 #pragma unroll 4
-    for (uint32_t k = (uint32_t)c0 + threadIdx.x; k < end; k += kBlock)
-      lds[k - c0] = (TACC)ldval<NT>(M.val, k) * gather(ldstream<NT>(M.ci, k));
+    for (int k = (int)threadIdx.x; k < m; k += kBlock)
+      lds[k] = (TACC)ldval<NT>(M.val, (int64_t)c0 + k) * gather(ldstream<NT>(M.ci, (int64_t)c0 + k));
   } else {
-    for (uint32_t c = (uint32_t)c0 + threadIdx.x; c < end; c += U * kBlock) {
+    for (int c = (int)threadIdx.x; c < m; c += U * kBlock) {
       int32_t col[U];
       TACC v[U];
       decltype(gather(0)) x[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const uint32_t k = min(c + u * kBlock, end - 1);
+        const int64_t k = (int64_t)c0 + min(c + u * kBlock, m - 1);
         col[u] = ldstream<NT>(M.ci, k);
         v[u] = (TACC)ldval<NT>(M.val, k);
       }
@@ -193,7 +195,7 @@ __device__ __forceinline__ void stage_products(const Mat<TM> &M, int c0, int c1,
       for (int u = 0; u < U; ++u) x[u] = gather(col[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (c + u * kBlock < end) lds[c + u * kBlock - c0] = v[u] * x[u];
+        if (c + u * kBlock < m) lds[c + u * kBlock] = v[u] * x[u];
     }
   }
 }
