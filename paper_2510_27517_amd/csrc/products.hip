@@ -14,12 +14,15 @@ namespace pcgk {
 // y[row] = (TY) v, v = the row's sum in TV, or a sum + b z[row] with AXPY; x, y
 // and z in FP64 or TV: the caller's FP64 vectors are read and written in
 // place, converted as they are gathered, with no copies around the product.
-template <typename TV, typename TM, typename TX, typename TY, bool AXPY>
+// FMT: sliced diagonals have kernels of their own; built with the others, a change
+// to the staging of CSR blocks slowed their nontemporal walk (128^3, G x: 29.3 ->
+// 32.5 us).
+template <typename TV, typename TM, typename TX, typename TY, bool AXPY, int FMT>
 __global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_spmv(DevCSR Md, const TX *__restrict__ x_,
                                                               TY *__restrict__ y_, TV a, TV b,
                                                               const double *__restrict__ z_) {
   __shared__ TV lds[kLdsBytes / sizeof(TV)];
-  const Mat<TM> M = mat<TM>(Md);
+  const Mat<TM> M = mat<TM, FMT>(Md);
   GLOBAL const TX *__restrict__ x = gl(x_);
   GLOBAL TY *__restrict__ y = gl(y_);
   GLOBAL const double *z = gl(z_);
@@ -62,16 +65,16 @@ __device__ __forceinline__ void loss_terms(double (&acc)[5], double w, double y,
 // lane: with four, the waves drift further apart and A's product re-reads
 // more (202 us), with eight 278. Over one probe per lane four: those are the
 // launches of few waves or of an odd count, where latency binds (20,000 rows of
-// 100, 7 probes: 0.90 of the time with two). 3x3 blocks go a block at a time, with
-// one index and no division per entry (elasticity 24^3, 32 probes: 233 -> 170
+// 100, 7 probes: 0.90 of the time with two). 3x3 blocks go a block at a time in
+// kernels of their own (BSR), with one index and no division per entry (elasticity 24^3, 32 probes: 233 -> 170
 // us). thin: a loss launch with little more than one turn of rows per wave gives
 // a workgroup's waves rows apart, so that no CU takes two full workgroups while
 // others have one (elasticity 8^3, 8 probes: 66 -> 52 us).
-template <typename TM, int LPR, int PV, int NT, bool LOSS>
+template <typename TM, int LPR, int PV, int NT, bool LOSS, bool BSR>
 __device__ __forceinline__ void spmm(const DevCSR &Md, int32_t k, GLOBAL const double *X, int32_t ldx, double c,
                                      GLOBAL const double *Z, int32_t ldz, double d, GLOBAL double *Y, int32_t ldy,
                                      double na, GLOBAL double *part, int32_t ldp, double *sh) {
-  const Mat<TM> M = mat<TM>(Md);
+  const Mat<TM> M = mat<TM, BSR ? FMT_BSR3 : -1>(Md);
   constexpr int RPW = 64 / LPR, NW = NT / 64, CH = LPR * PV;
   const int lane = threadIdx.x & 63, grp = lane / LPR, pl = (lane % LPR) * PV;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -118,7 +121,7 @@ __device__ __forceinline__ void spmm(const DevCSR &Md, int32_t k, GLOBAL const d
           for (; e + 4 <= len; e += 4) batch(e, len, std::integral_constant<int, 4>{}, entry);
         for (; e < len; e += 2) batch(e, len, std::integral_constant<int, 2>{}, entry);
       };
-      if (M.fmt == FMT_SDIA) {  // one offset per slice entry; stored zeros add +0
+      if (!BSR && M.fmt == FMT_SDIA) {  // one offset per slice entry; stored zeros add +0
         const int sl = __builtin_amdgcn_readfirstlane(min(base, M.n - 1) / kSliceRows);
         const int o0 = ro(M.blk)[sl], wd = ro(M.blk)[sl + 1] - o0;
         GLOBAL const TM *vv = M.val + (int64_t)o0 * kSliceRows + row % kSliceRows;
@@ -126,7 +129,7 @@ __device__ __forceinline__ void spmm(const DevCSR &Md, int32_t k, GLOBAL const d
           col = min(max(row + ro(M.ci)[o0 + e], 0), M.n - 1);
           a = ld64(vv, (int64_t)e * kSliceRows);
         });
-      } else if (M.fmt == FMT_BSR3) {  // a block at a time: three entries of the row
+      } else if (BSR) {  // a block at a time: three entries of the row
         const int32_t R = row / 3, sub = row % 3, sl = R / kBSliceRows, rr = R % kBSliceRows;
         const int32_t o0 = M.blk[sl], wd = M.blk[sl + 1] - o0;
         GLOBAL const int32_t *bc = M.ci + (int64_t)o0 * kBSliceRows + rr;
@@ -217,11 +220,11 @@ __device__ __forceinline__ void spmm(const DevCSR &Md, int32_t k, GLOBAL const d
   }
 }
 
-template <typename TM, int LPR, int PV>
+template <typename TM, int LPR, int PV, bool BSR>
 __global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_spmm(DevCSR M, int32_t k, const double *X, int32_t ldx, double c,
                                                               const double *Z, int32_t ldz, double d, double *Y,
                                                               int32_t ldy) {
-  spmm<TM, LPR, PV, kBlock, false>(M, k, gl(X), ldx, c, Z ? gl(Z) : nullptr, ldz, d, gl(Y), ldy, 1.0, nullptr, 0,
+  spmm<TM, LPR, PV, kBlock, false, BSR>(M, k, gl(X), ldx, c, Z ? gl(Z) : nullptr, ldz, d, gl(Y), ldy, 1.0, nullptr, 0,
                                    nullptr);
 }
 
@@ -229,12 +232,12 @@ __global__ __launch_bounds__(kBlock) PCG_OCCUPANCY void k_spmm(DevCSR M, int32_t
 // q) k + p] for workgroup b < kLossGrid (two large workgroups per CU, so that
 // the partial sums stay few while every wave slot is taken).
 constexpr int kLossThreads = 1024;
-template <typename TM, int LPR, int PV>
+template <typename TM, int LPR, int PV, bool BSR>
 __global__ __launch_bounds__(kLossThreads) PCG_OCCUPANCY void k_spmm_loss(DevCSR M, int32_t k, const double *X,
                                                                          int32_t ldx, const double *W, int32_t ldw,
                                                                          double na, double *part, int32_t ldp) {
   __shared__ double sh[kLossThreads / 64 * LPR * PV];
-  spmm<TM, LPR, PV, kLossThreads, true>(M, k, gl(X), ldx, 1.0, gl(W), ldw, 0.0, nullptr, 0, na, gl(part), ldp, sh);
+  spmm<TM, LPR, PV, kLossThreads, true, BSR>(M, k, gl(X), ldx, 1.0, gl(W), ldw, 0.0, nullptr, 0, na, gl(part), ldp, sh);
 }
 
 // One wave per probe: the workgroups' partial sums, each lane's in ascending
@@ -272,15 +275,24 @@ __global__ __launch_bounds__(64) void k_loss_final(int32_t k, const double *__re
     default: return hipErrorInvalidValue;                  \
   }
 
+template <typename TV, typename TM, typename TX, typename TY, int FMT>
+static void launch_product_as(const DevCSR &M, const void *x, void *y, const double *z, double a, double b,
+                              hipStream_t s) {
+  if (z)
+    hipLaunchKernelGGL((k_spmv<TV, TM, TX, TY, true, FMT>), dim3(M.grid), dim3(kBlock), 0, s, M, (const TX *)x, (TY *)y,
+                       (TV)a, (TV)b, z);
+  else
+    hipLaunchKernelGGL((k_spmv<TV, TM, TX, TY, false, FMT>), dim3(M.grid), dim3(kBlock), 0, s, M, (const TX *)x,
+                       (TY *)y, (TV)0, (TV)0, z);
+}
+
 template <typename TV, typename TM, typename TX, typename TY>
 static hipError_t launch_product(const DevCSR &M, const void *x, void *y, const double *z, double a, double b,
                                  hipStream_t s) {
-  if (z)
-    hipLaunchKernelGGL((k_spmv<TV, TM, TX, TY, true>), dim3(M.grid), dim3(kBlock), 0, s, M, (const TX *)x, (TY *)y,
-                       (TV)a, (TV)b, z);
+  if (M.fmt == FMT_SDIA)
+    launch_product_as<TV, TM, TX, TY, FMT_SDIA>(M, x, y, z, a, b, s);
   else
-    hipLaunchKernelGGL((k_spmv<TV, TM, TX, TY, false>), dim3(M.grid), dim3(kBlock), 0, s, M, (const TX *)x, (TY *)y,
-                       (TV)0, (TV)0, z);
+    launch_product_as<TV, TM, TX, TY, -1>(M, x, y, z, a, b, s);
   return hipGetLastError();
 }
 
@@ -309,14 +321,15 @@ hipError_t launch_spmv(const Types &ty, const DevCSR &M, int x_dtype, const void
 // lane: elasticity 36^3, 8,748 waves, 161 and 232 us; 20,000 rows of 100, 1,250
 // waves, 216 and 112; elasticity 8^3, 96 waves, 74 and 51; P P^T of 18,000 over 16,
 // 2,250 waves, 141 and 108), and more than two probes, which would leave every other
-// lane idle (100^3: 91 and 77).
+// lane idle (100^3: 91 and 77). Above 64 probes, where a row takes a whole wave
+// either way, they pair up always (60^2, 100 probes: 47 and 52).
 static void spmm_shape(int32_t n, int32_t k, int &lpr, bool &pair) {
   auto fit = [](int32_t m) {
     int l = 2;
     while (l < m && l < 64) l *= 2;
     return l;
   };
-  pair = k > 2 && k % 2 == 0 && (int64_t)n * fit(k / 2) / 64 >= 4096;
+  pair = k > 2 && k % 2 == 0 && (k > 64 || (int64_t)n * fit(k / 2) / 64 >= 4096);
   lpr = fit(pair ? k / 2 : k);
 }
 
@@ -354,8 +367,12 @@ hipError_t launch_spmm(const DevCSR &M, int32_t k, const double *X, int32_t ldx,
   if (M.n <= 0 || k <= 0) return hipSuccess;
   PCG_PROD_M(M.dtype, TM, PCG_SPMM_SHAPE(M.n, k, LPR, PV, {
     const int grid = spmm_grid(M.n, kBlock / LPR, kSpmmGrid);
-    hipLaunchKernelGGL((k_spmm<TM, LPR, PV>), dim3(grid), dim3(kBlock), 0, s, M, k, X, ldx, c, Z, ldz, d, Y,
-                       ldy);
+    if (M.fmt == FMT_BSR3)
+      hipLaunchKernelGGL((k_spmm<TM, LPR, PV, true>), dim3(grid), dim3(kBlock), 0, s, M, k, X, ldx, c, Z, ldz, d, Y,
+                         ldy);
+    else
+      hipLaunchKernelGGL((k_spmm<TM, LPR, PV, false>), dim3(grid), dim3(kBlock), 0, s, M, k, X, ldx, c, Z, ldz, d, Y,
+                         ldy);
   }));
   return hipGetLastError();
 }
@@ -363,18 +380,22 @@ hipError_t launch_spmm(const DevCSR &M, int32_t k, const double *X, int32_t ldx,
 hipError_t launch_spmm_loss(const DevCSR &M, int32_t k, const double *X, int32_t ldx, const double *W, int32_t ldw,
                             double na, double *part, int32_t ldp, hipStream_t s) {
   if (M.n <= 0 || k <= 0) return hipSuccess;
+#define PCG_LOSS(TM)                                                                                              \
+  PCG_SPMM_SHAPE(M.n, k, LPR, PV, {                                                                               \
+    if (M.fmt == FMT_BSR3)                                                                                        \
+      hipLaunchKernelGGL((k_spmm_loss<TM, LPR, PV, true>), dim3(kLossGrid), dim3(kLossThreads), 0, s, M, k, X, ldx, \
+                         W, ldw, na, part, ldp);                                                                  \
+    else                                                                                                          \
+      hipLaunchKernelGGL((k_spmm_loss<TM, LPR, PV, false>), dim3(kLossGrid), dim3(kLossThreads), 0, s, M, k, X,    \
+                         ldx, W, ldw, na, part, ldp);                                                             \
+  })
   if (M.dtype == F64)
-    PCG_SPMM_SHAPE(M.n, k, LPR, PV, {
-      hipLaunchKernelGGL((k_spmm_loss<double, LPR, PV>), dim3(kLossGrid), dim3(kLossThreads), 0, s, M, k, X, ldx,
-                         W, ldw, na, part, ldp);
-    });
+    PCG_LOSS(double);
   else if (M.dtype == F32)
-    PCG_SPMM_SHAPE(M.n, k, LPR, PV, {
-      hipLaunchKernelGGL((k_spmm_loss<float, LPR, PV>), dim3(kLossGrid), dim3(kLossThreads), 0, s, M, k, X, ldx,
-                         W, ldw, na, part, ldp);
-    });
+    PCG_LOSS(float);
   else
     return hipErrorInvalidValue;
+#undef PCG_LOSS
   return hipGetLastError();
 }
 
